@@ -95,6 +95,24 @@ __device__ __forceinline__ void g_and(GLOBAL T *p, T v) {
     (void)__hip_atomic_fetch_and(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// The thread's index, opaque to the compiler: addresses and predicates formed
+// from it are not carried from visit to visit in registers.
+__device__ __forceinline__ int thread_id() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    __builtin_assume(t >= 0 && t < kThreads);
+    return t;
+}
+__device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
+__device__ __forceinline__ int bits(unsigned long long m) { return (int)__popcll(m); }
+// Set bits of a wave's mask below the calling lane.
+__device__ __forceinline__ int prefix_count(unsigned long long m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
+// The LDS serves a wave's accesses in program order: only the compiler has to
+// keep them in that order.
+__device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+
 template <int TW, int TH>
 struct Geo {
     static constexpr int NT = kThreads;
@@ -248,7 +266,7 @@ __device__ __forceinline__ void terminal_caps(const TermIn &t, long long lam, lo
 template <int K, int TW, int TH>
 __device__ void orient_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl, int *s_red) {
     using G = Geo<TW, TH>;
-    const int tid = threadIdx.x, lx = tid % TW, ly0 = tid / TW;
+    const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
     const int W = D.W, H = D.H;
@@ -292,7 +310,7 @@ template <int K, int TW, int TH>
 __device__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl,
                           int *s_red, unsigned long long *s_sum) {
     using G = Geo<TW, TH>;
-    const int tid = threadIdx.x, lx = tid % TW, ly0 = tid / TW;
+    const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
     const int W = D.W, H = D.H, n = D.n;
@@ -386,30 +404,31 @@ __device__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, 
 }
 
 // ---------------------------------------------------------------------------
-// kSweep: tile-local push/relabel iterations in LDS.
+// kSweep: tile-local push/relabel in LDS.
 //
 // The tile's residuals (one record of K words per cell, so that a pixel reads
 // all of them at once), excess, sink residuals and heights live in LDS with a
-// one-pixel halo.  In every inner iteration each active pixel p (e > 0,
-// h < H_INF) pushes d = min(e, r) to the sink when rt > 0 and along
-// admissible arcs (h(p) = h(q) + 1), then, if excess is left and no
-// admissible arc, relabels to 1 + min h(q) over its residual arcs.  Only the
-// active pixels are processed (a small fraction of the tile once the first
-// iterations are done).  All residual and excess updates are LDS atomics
-// without return: whatever the interleaving of neighbours, every update is
+// one-pixel halo.  An active pixel p (e > 0, h < H_INF) pushes d = min(e, r)
+// to the sink when rt > 0 and along admissible arcs (h(p) = h(q) + 1) and, if
+// excess is left and no arc is admissible, is lifted to 1 + min h(q) over its
+// residual arcs.  Only the active pixels are processed (a small fraction of
+// the tile once the first steps are done).  All residual and excess updates
+// are LDS atomics: whatever the interleaving of neighbours, every update is
 // applied exactly once, a pixel never sends more than the excess and residual
-// it read (other threads only add to those), so the bookkeeping stays exact
+// it read (other lanes only add to those), so the bookkeeping stays exact
 // and non-negative.  Labels are only a guide here; maximality is
 // certified by the exact global relabel.  A push to a halo pixel (another
 // tile) lands in the halo cell's word of the reverse arc, i.e. exactly the
 // amount handed over; those words go to the neighbours' inboxes at the end.
+// Only the cells that the visit changed are written back (in the tail some
+// 100 of the 1024).
 // ---------------------------------------------------------------------------
 template <int K, int TW, int TH, bool GAP>
 __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl,
                            int iters, int xsw, int32_t *lds, int *s_red) {
     using G = Geo<TW, TH>;
     constexpr int PPT = G::PPT, RPI = G::RPI, HW = G::HW, HH = G::HH, HALO = G::HALO;
-    const int tid = threadIdx.x, lx = tid % TW, ly0 = tid / TW;
+    const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
     const int W = D.W, H = D.H, n = D.n;
@@ -419,9 +438,13 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
     int32_t *sh_t = lds + 2 * HALO;  // [HALO] sink residuals (tile cells only)
     int32_t *sh_r = lds + 3 * HALO;  // [HALO][K] residuals; halo cells: pushes handed over
     __shared__ int s_nb[9];
-    __shared__ uint16_t s_slot[kThreads * PPT + kThreads];  // per wave: its active pixels' cells; then one spare word per thread
+    constexpr int kRing = 256;
+    // a bit per cell whose excess moved in this visit (only it and its neighbours changed)
+    __shared__ uint32_t s_dirty[(HALO + 31) / 32];
+    __shared__ uint16_t s_slot[kThreads / 64 * kRing];  // per wave: cells of active pixels waiting for a lane
 
     if (tid < 9) s_nb[tid] = 0;
+    if (tid < (HALO + 31) / 32) s_dirty[tid] = 0u;
     if (tid == 0) g_and(&gp(D.tile_act)[tl], ~2u);  // about to drain the inbox
     // Every global load of the visit is issued before any is used: the halo
     // cell heights of the neighbour tiles (one ring cell per thread), the
@@ -476,6 +499,7 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
         sh_h[hc] = hin && hv <= gap ? hv : kHInf;
 #pragma unroll
         for (int k = 0; k < K; ++k) sh_r[hc * K + k] = 0;  // hand-over words
+        sh_e[hc] = 1;  // never activated by a push
     }
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
@@ -495,6 +519,7 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
             const int c = (by + 1) * HW + bx + 1;
             atomicAdd(&sh_e[c], ibv[q]);
             atomicAdd(&sh_r[c * K + k], ibv[q]);
+            atomicOr(&s_dirty[c >> 5], 1u << (c & 31));
         }
     }
     __syncthreads();
@@ -549,93 +574,125 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
                 const int c = (by + 1) * HW + bx + 1;
                 atomicAdd(&sh_e[c], v);
                 atomicAdd(&sh_r[c * K + k], v);
+                atomicOr(&s_dirty[c >> 5], 1u << (c & 31));
             }
         }
         __syncthreads();
     };
-    const int xperiod = xsw > 0 ? max(1, iters / (xsw + 1)) : iters + 1;
-
-    // Iterations.  Every pixel belongs to one wave (the PPT pixels of each of
-    // its lanes).  Per iteration a wave lists its active pixels (e > 0,
-    // h < H_INF) in a slot array of its own, then its lanes take one listed
-    // pixel each: sink push, pushes along admissible arcs in arc order, lift
-    // if excess is left.  Work is proportional to the active pixels, and
-    // waves need no barrier between iterations: every cross-pixel update is
-    // an LDS atomic, and a pixel's height and sink residual are written only
-    // by its own wave.
-    const int lane = tid & 63;
-    uint16_t *slot = s_slot + (tid >> 6) * (PPT * 64);
-    for (int it = 0; it < iters; ++it) {
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        int ev[PPT], hv[PPT];
+    // Walking.  Every active pixel (e > 0, h < H_INF) has one token, and a lane
+    // that holds a pixel's token is the only one that takes excess out of it,
+    // pushes along its arcs and lifts it.  A step of the lane is: a push to
+    // the sink, then a push along the first admissible arc, or, if there is
+    // none and excess is left, a lift.  The excess leaves the pixel with the
+    // step's last atomic, whose reply tells whether the pixel is still active
+    // (the lane keeps the token); a push into a pixel whose excess was zero
+    // creates that pixel's token.  The lane goes on with the pixel it
+    // activated, and queues its own if that stays active, in its wave's
+    // ring, from which lanes without a token refill.
+    //
+    // Why: a sweep is bound by the latency of its steps (a wave works on some
+    // 15 pixels at a time, few of its lanes).  A step is two LDS round trips
+    // and some 60 instructions, 0.43 us; listing the tile's active pixels by
+    // ballots before each step, with a workgroup vote to end, was 1.1 us.
+    // All admissible arcs in one step made it 0.56 us at 4 arcs and 0.95 at
+    // 8, for few steps less.  Waves need no barrier: one without tokens is
+    // done, since nobody hands it any.  A token that finds the ring full is
+    // dropped: its pixel waits for the next visit.
+    constexpr int RC = kRing;  // ring entries per wave
+    uint16_t *ring = s_slot + (tid >> 6) * RC;
+    for (int seg = 0; seg <= xsw; ++seg) {
+        int head = 0, cnt = 0;
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             const int c = (ly0 + j * RPI + 1) * HW + lx + 1;
-            ev[j] = sh_e[c];
-            hv[j] = sh_h[c];
-        }
-        int na = 0;
-#pragma unroll
-        for (int j = 0; j < PPT; ++j) {
-            const int c = (ly0 + j * RPI + 1) * HW + lx + 1;
-            const bool a = (ev[j] > 0) & (hv[j] < kHInf);
+            const bool a = (sh_e[c] > 0) & (sh_h[c] < kHInf);
             const unsigned long long m = __ballot(a);
-            // listed lanes below this one (hardware prefix count), and no
-            // branch: every lane writes, the unlisted ones to a word of their own
-            const int below_n =
-                (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-            const int at = a ? (tid >> 6) * (PPT * 64) + na + below_n : kThreads * PPT + tid;
-            s_slot[at] = (uint16_t)c;
-            na += __popcll(m);
+            const int at = cnt + prefix_count(m);
+            if (a) ring[at] = (uint16_t)c;
+            cnt += bits(m);
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-        for (int i = lane; i < na; i += 64) {
-            const int c = slot[i];
-            int r[K], hq[K];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                r[k] = sh_r[c * K + k];
-                hq[k] = sh_h[c + DYk(k) * HW + DXk(k)];
+        __syncthreads();  // every wave has listed its pixels: from here on a token is never given twice
+        static_assert(PPT * 64 <= RC && (RC & (RC - 1)) == 0, "a wave's pixels fit its ring");
+        // an iteration is as many steps as the wave needs for one step of
+        // each listed pixel
+        int steps = (xsw > 0 ? max(1, iters / (xsw + 1)) : iters) * ((cnt + 63) >> 6);
+        steps = __builtin_amdgcn_readfirstlane(steps);
+        int c = 0;  // the pixel whose token the lane holds (0: none; cell 0 is a corner of the halo)
+        for (; steps > 0; --steps) {
+            if (cnt > 0) {
+                const unsigned long long idle = __ballot(c == 0);
+                const int below = prefix_count(idle);
+                lds_order();
+                if (c == 0 && below < cnt) c = ring[(head + below) & (RC - 1)];
+                const int took = imin(cnt, bits(idle));
+                head += took;
+                cnt -= took;
             }
-            const int h = sh_h[c];
-            const int rt = sh_t[c];
-            // the excess only grew since the listing (only this lane takes it
-            // out), so it is still positive
-            int ex = sh_e[c];
-            const int dt = ex < rt ? ex : rt;
-            ex -= dt;
-            if (dt) sh_t[c] = rt - dt;
-            int pushed = dt;
-            const int hm1 = h - 1;
-            int mn = kHInf;
+            if (__ballot(c != 0) == 0ull) break;
+            int next = 0;       // the pixel the lane goes on with
+            bool again = false;  // the lane's pixel is to be queued
+            if (c != 0) {
+                int r[K], hq[K];
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int rk = r[k];
-                const bool down = hq[k] == hm1;
-                const int d = down ? (rk < ex ? rk : ex) : 0;  // residuals are never negative
-                ex -= d;
-                pushed += d;
-                const int cand = rk - d > 0 ? hq[k] + 1 : kHInf;
-                mn = cand < mn ? cand : mn;
-                if (d) {
-                    const int q = c + DYk(k) * HW + DXk(k);
-                    atomicSub(&sh_r[c * K + k], d);
-                    atomicAdd(&sh_r[q * K + (k ^ 1)], d);
-                    // halo cells' excess words are never read: no test needed
-                    atomicAdd(&sh_e[q], d);
+                for (int k = 0; k < K; ++k) {
+                    r[k] = sh_r[c * K + k];
+                    hq[k] = sh_h[c + DYk(k) * HW + DXk(k)];
                 }
+                const int h = sh_h[c];
+                const int rt = sh_t[c];
+                // other lanes only add to the excess and the residuals
+                int ex = sh_e[c];
+                atomicOr(&s_dirty[c >> 5], 1u << (c & 31));
+                const int dt = imin(ex, rt);
+                ex -= dt;
+                if (dt) sh_t[c] = rt - dt;
+                const int hm1 = h - 1;
+                int rk = 0, to = 0;  // the first admissible arc: its residual; its cell offset and number
+#pragma unroll
+                for (int k = K - 1; k >= 0; --k) {
+                    const bool down = (hq[k] == hm1) & (r[k] > 0);
+                    rk = down ? r[k] : rk;
+                    to = down ? (DYk(k) * HW + DXk(k)) * 8 + k : to;
+                }
+                const int d = imin(ex, rk);
+                int was = 1, nh = h;
+                if (d > 0) {
+                    const int k = to & 7;
+                    next = c + (to >> 3);
+                    atomicSub(&sh_r[c * K + k], d);
+                    atomicAdd(&sh_r[next * K + (k ^ 1)], d);
+                    was = atomicAdd(&sh_e[next], d);  // halo cells hold 1: never activated
+                } else if (ex > 0) {
+                    // the sink arc and every admissible arc are saturated:
+                    // lift above the lowest residual neighbour
+                    int mn = kHInf;
+#pragma unroll
+                    for (int k = 0; k < K; ++k) {
+                        const int cand = r[k] > 0 ? hq[k] + 1 : kHInf;
+                        mn = cand < mn ? cand : mn;
+                    }
+                    nh = mn >= hcap ? kHInf : mn;
+                    sh_h[c] = nh;
+                }
+                lds_order();
+                const int out = dt + d;
+                const int rest = atomicSub(&sh_e[c], out) - out;
+                // the reply of the push is waited for together with this one
+                asm volatile("" : "+v"(was));
+                const bool keep = (rest > 0) & (nh < kHInf);
+                again = keep & (was == 0);
+                next = was == 0 ? next : keep ? c : 0;
             }
-            if (pushed) atomicSub(&sh_e[c], pushed);
-            // excess left means the sink arc and every admissible arc are
-            // saturated: lift above the lowest residual neighbour
-            if (ex > 0) sh_h[c] = mn >= hcap ? kHInf : mn;
+            const unsigned long long m = __ballot(again);
+            if (m != 0ull) {
+                const int at = cnt + prefix_count(m);  // entries beyond the ring are dropped
+                if (again && at < RC) ring[(head + at) & (RC - 1)] = (uint16_t)c;
+                cnt = imin(RC, cnt + bits(m));
+            }
+            c = next;
+            lds_order();
         }
-        // progress check every 2 iterations: an iteration in which no wave
-        // listed a pixel changed nothing, so the tile is at rest
-        if ((it & 1) == 1 || it + 1 == iters) {
-            if (!block_any(na > 0, s_red + 16 + 4 * ((it >> 1) & 1))) break;
-        }
-        if ((it + 1) % xperiod == 0 && it + 1 < iters) exchange();
+        if (seg < xsw) exchange();
     }
     __syncthreads();
 
@@ -666,6 +723,13 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
                 if (h < D.hsize) g_add(&gp(D.hist)[h], 1);
             }
         }
+        uint32_t moved = s_dirty[c >> 5] >> (c & 31);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int q = c + DYk(k) * HW + DXk(k);
+            moved |= s_dirty[q >> 5] >> (q & 31);
+        }
+        if (!(moved & 1u)) continue;  // as it was
         const int rt = sh_t[c];
         int rm = (rt > 0 ? kRtBit : 0) | (e > 0 ? kEBit : 0);
 #pragma unroll
@@ -732,7 +796,7 @@ __device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *
                              int sub, int xrounds, int32_t *lds, int *s_red) {
     using G = Geo<TW, TH>;
     constexpr int PPT = G::PPT, RPI = G::RPI, HW = G::HW;
-    const int tid = threadIdx.x, lx = tid % TW, ly0 = tid / TW;
+    const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
     const int W = D.W, H = D.H, n = D.n;
@@ -984,7 +1048,7 @@ __device__ void cut_tile_swapped(const StepParams &P, const InstDesc &D, InstSta
                                  int *s_red, unsigned long long *s_sum) {
     using G = Geo<TW, TH>;
     constexpr int PPT = G::PPT, RPI = G::RPI;
-    const int tid = threadIdx.x, lx = tid % TW, ly0 = tid / TW;
+    const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
     const int W = D.W, H = D.H, n = D.n;
@@ -1055,7 +1119,7 @@ __device__ void cut_tile(const StepParams &P, const InstDesc &D, InstState *S, i
                          int kk, int xrounds, int32_t *lds, int *s_red, unsigned long long *s_sum) {
     using G = Geo<TW, TH>;
     constexpr int PPT = G::PPT, RPI = G::RPI, HW = G::HW;
-    const int tid = threadIdx.x, lx = tid % TW, ly0 = tid / TW;
+    const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
     const int W = D.W, H = D.H, n = D.n;
