@@ -63,7 +63,12 @@ typedef struct pmf_options {
     int32_t local_bfs_iters;    /* bound on relaxation rounds between halo reads     */
     int32_t steps_per_sync;     /* supersteps per host completion check              */
     int64_t max_supersteps;     /* per-instance budget; exceeding it = PMF_ETIMEOUT  */
-    int32_t use_graph;          /* 1: replay supersteps from a captured hipGraph     */
+    int32_t use_graph;          /* 1: the device drives the solve: instances run     */
+                                /*   their supersteps inside one launch, tiles going */
+                                /*   to whichever workgroups are free (instances of  */
+                                /*   up to 640 tiles; larger ones: supersteps        */
+                                /*   replayed from a captured hipGraph); 0: every    */
+                                /*   superstep launched by the host                  */
     int32_t order;              /* 0: FIFO packing order, 1: LPT (largest first)     */
     int64_t mem_budget;         /* bytes the library may allocate (0 = no limit)     */
     int32_t max_slots;          /* instance slots of a serving session (0 = 4096)    */
@@ -148,7 +153,7 @@ typedef struct pmf_handle pmf_handle;
 
 /* Per-handle counters of the last solve (or of the session so far). */
 typedef struct pmf_stats {
-    int64_t supersteps;       /* device launches of the superstep kernel            */
+    int64_t supersteps;       /* supersteps run (the most that one instance ran)    */
     int64_t sweep_visits;     /* tile visits that ran push/relabel iterations       */
     int64_t global_relabels;  /* completed global relabels (all instances)          */
     int64_t bfs_passes;       /* tile-parallel relaxation passes (relabel + cut)    */
@@ -211,8 +216,7 @@ int pmf_solve_batch(pmf_handle *h, const pmf_instance *inst, int32_t n_inst, int
  * PMF_NOALLOC_BYTES that the library holds on each device it runs on until
  * the process ends.  Arguments, results and errors are those of
  * pmf_solve_batch, and so are the flows and masks; the call itself allocates
- * no device memory (it launches supersteps directly, without capturing a
- * graph).  A batch whose state does not fit returns PMF_ELIMIT before any
+ * no device memory.  A batch whose state does not fit returns PMF_ELIMIT before any
  * launch; options.timing must be 0 (else PMF_EINVAL).  Masks stay readable
  * with pmf_extract_cut / pmf_extract_levels until the next solve on this
  * handle or the next no-allocation solve on this device: every handle on a

@@ -54,7 +54,8 @@ enum Orientation : int32_t {
 
 struct alignas(16) InstDesc {
     int32_t W, H, K, n;
-    int32_t tiles_x, tiles_y, ntiles, tile0;
+    int32_t tiles_x, tiles_y, ntiles;
+    int32_t tile0;       // 64-byte line of the instance's share of StepParams::lists (device-driven solve)
     int32_t L, slot_id;
     int32_t check_prev;  // lambdas[-1] belongs to the same schedule: check it too
     int32_t tile_w;      // tile width in pixels (tiles hold 1024 pixels)
@@ -170,6 +171,32 @@ constexpr int kBarAbort = 18, kBarSteps = 19;
 int persist_workgroups(int tile_w, int kset);
 int launch_persist(const StepParams *p_dev, int tile_w, int kset, int grid, int max_steps, int exit_tiles,
                    void *stream);
+
+// The device-driven solve: one launch in which every instance of the work
+// list runs up to `quota` supersteps of its own (tiles claimed by whichever
+// workgroups are free).  Memory: engine_bytes() for the words below, and the
+// list memory of StepParams for the tile lists, where InstDesc::tile0 is the
+// 64-byte line at which the instance's share starts.
+struct EngineParams {
+    int32_t *live;        // [8 * 32] per XCD: tiles of the instances still running (one word per 128 bytes)
+    int32_t *rounds;      // most supersteps an instance ran in this launch
+    unsigned long long *avail;  // [8][avail_words] per XCD: a bit per work-list entry with unclaimed tiles
+    int32_t *sync;        // [work list][kEngSync] claim, done and info words
+    int32_t avail_words;  // a multiple of 16
+    int32_t quota;
+};
+constexpr int kEngSync = 96;  // words of an instance's three lines
+enum { kSyClaim = 0, kSyDone = 32, kSyInfo = 64 };
+enum { kInPhase, kInSwap, kInSub, kInK, kInReps, kInXsw, kInLeft, kEngInfo };
+constexpr int kEngLine = 16;  // words of a line of the list memory
+constexpr size_t engine_clear_bytes(int avail_words) { return 8 * 128 + 128 + 8 * (size_t)avail_words * 8; }
+constexpr int engine_words(int n) { return (n + 1023) / 1024 * 16; }
+constexpr size_t engine_bytes(int n) { return engine_clear_bytes(engine_words(n)) + (size_t)n * kEngSync * 4; }
+constexpr int kEngineSlots = 4096;    // instances that every handle has room for from the start
+constexpr int kEngineMax = 1 << 16;   // and at most
+constexpr int kEngineTiles = 640;     // tiles of the largest instance it is used for
+int engine_workgroups(int tile_w, int kset);
+int launch_engine(const StepParams &p, const EngineParams &e, int tile_w, int kset, int grid, void *stream);
 
 // out[p] (+)= number of the L masks that hold pixel p (n pixels).
 int launch_levels(const uint8_t *masks, int L, int n, uint8_t *out, bool accumulate, void *stream);

@@ -39,6 +39,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "pmf.h"
 #include "pmf_border.h"
@@ -74,6 +75,9 @@ __device__ __forceinline__ InstDesc load_desc(const InstDesc *table, int slot) {
     for (int i = 0; i < (int)(sizeof(InstDesc) / 4); ++i) dst[i] = src[i];
     return d;
 }
+__device__ __forceinline__ int32_t desc_word(const InstDesc *table, int slot, int32_t InstDesc::*field) {
+    return *(const __attribute__((address_space(4))) int32_t *)&(table[slot].*field);
+}
 template <typename T>
 __device__ __forceinline__ T ld_agent(GLOBAL const T *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -95,6 +99,23 @@ __device__ __forceinline__ void g_and(GLOBAL T *p, T v) {
     (void)__hip_atomic_fetch_and(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Access to instance state that other workgroups write or read within the
+// same launch.  COH (the device-driven solve): agent-scope accesses, whose
+// stores go through to where every XCD sees them and whose loads never take an
+// old copy; a store is complete once its wave's vector-memory counter is zero
+// (stores_done).  Otherwise (one superstep per launch) plain accesses: the
+// launch boundary orders them.
+template <bool COH, typename T>
+__device__ __forceinline__ T ldc(GLOBAL const T *p) {
+    return COH ? ld_agent(p) : *p;
+}
+template <bool COH, typename T>
+__device__ __forceinline__ void stc(GLOBAL T *p, T v) {
+    if (COH)
+        st_agent(p, v);
+    else
+        *p = v;
+}
 // The thread's index, opaque to the compiler: addresses and predicates formed
 // from it are not carried from visit to visit in registers.
 __device__ __forceinline__ int thread_id() {
@@ -112,6 +133,7 @@ __device__ __forceinline__ int prefix_count(unsigned long long m) {
 // The LDS serves a wave's accesses in program order: only the compiler has to
 // keep them in that order.
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 template <int TW, int TH>
 struct Geo {
@@ -264,7 +286,7 @@ __device__ __forceinline__ void terminal_caps(const TermIn &t, long long lam, lo
 // s-t swap is chosen from these counts), one pass before kInit.
 // ---------------------------------------------------------------------------
 template <int K, int TW, int TH>
-__device__ void orient_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl, int *s_red) {
+__device__ __forceinline__ void orient_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl, int *s_red) {
     using G = Geo<TW, TH>;
     const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
@@ -306,8 +328,8 @@ __device__ void orient_tile(const StepParams &P, const InstDesc &D, InstState *S
 //   the common part m = min(cs, ct) goes straight from s to t: e = cs - m,
 //   rt = ct - m; r_k = n-link capacity; inbox cleared.
 // ---------------------------------------------------------------------------
-template <int K, int TW, int TH>
-__device__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl,
+template <int K, int TW, int TH, bool COH>
+__device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl, bool swap,
                           int *s_red, unsigned long long *s_sum) {
     using G = Geo<TW, TH>;
     const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
@@ -316,7 +338,6 @@ __device__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, 
     const int W = D.W, H = D.H, n = D.n;
     const long long lam0 = gp(D.lambdas)[0];
     const long long lamL = gp(D.lambdas)[D.L - 1];
-    const bool swap = __builtin_amdgcn_readfirstlane(S->swap) != 0;
     const int32_t nlmax = ((1 << 30) - 1) / K;
     int err = 0;
     long long scs = 0;
@@ -371,17 +392,17 @@ __device__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, 
                 if (swap) c = on ? rv[jj][k] : 0;
                 if (!on || c < 0) c = 0;
                 if (c > nlmax) c = nlmax;
-                gp(D.r)[(size_t)k * n + p] = c;
+                stc<COH>(&gp(D.r)[(size_t)k * n + p], c);
                 if (c > 0) rm |= 1 << k;
             }
-            gp(D.e)[p] = e;
-            gp(D.rt)[p] = rt;
-            gp(D.h)[p] = rt > 0 ? 1 : kHInf;
-            gp(D.rmask)[p] = (uint16_t)rm;
+            stc<COH>(&gp(D.e)[p], e);
+            stc<COH>(&gp(D.rt)[p], rt);
+            stc<COH>(&gp(D.h)[p], rt > 0 ? 1 : kHInf);
+            stc<COH>(&gp(D.rmask)[p], (uint16_t)rm);
         }
     }
     for (int i = tid; i < Border<K, TW, TH>::E; i += kThreads)
-        gp(D.inbox)[(size_t)tl * Border<K, TW, TH>::E + i] = 0;
+        stc<COH>(&gp(D.inbox)[(size_t)tl * Border<K, TW, TH>::E + i], 0);
     if (tl == 0 && tid < 64) {
         // the schedule: lambda_0 >= 0, non-decreasing (also across the start
         // of a chunk of a longer schedule)
@@ -394,10 +415,10 @@ __device__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, 
     const long long tot = block_sum_i64(scs, s_sum);
     if (tid == 0) {
         if (tot) atomicAdd((unsigned long long *)&S->sum_cs, (unsigned long long)tot);
-        gp(D.tile_act)[tl] = 0;
-        gp(D.tile_cnt)[tl] = 0;
-        gp(D.tile_chg)[tl] = 1;
-        gp(D.tile_chg)[D.ntiles + tl] = 1;
+        stc<COH>(&gp(D.tile_act)[tl], 0u);
+        stc<COH>(&gp(D.tile_cnt)[tl], 0);
+        stc<COH>(&gp(D.tile_chg)[tl], (uint8_t)1);
+        stc<COH>(&gp(D.tile_chg)[D.ntiles + tl], (uint8_t)1);
     }
     if (err) atomicOr(&S->err, err);
     (void)s_red;
@@ -423,8 +444,8 @@ __device__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, 
 // Only the cells that the visit changed are written back (in the tail some
 // 100 of the 1024).
 // ---------------------------------------------------------------------------
-template <int K, int TW, int TH, bool GAP>
-__device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl,
+template <int K, int TW, int TH, bool GAP, bool COH>
+__device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl,
                            int iters, int xsw, int32_t *lds, int *s_red) {
     using G = Geo<TW, TH>;
     constexpr int PPT = G::PPT, RPI = G::RPI, HW = G::HW, HH = G::HH, HALO = G::HALO;
@@ -439,8 +460,7 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
     int32_t *sh_r = lds + 3 * HALO;  // [HALO][K] residuals; halo cells: pushes handed over
     __shared__ int s_nb[9];
     constexpr int kRing = 256;
-    // a bit per cell whose excess moved in this visit (only it and its neighbours changed)
-    __shared__ uint32_t s_dirty[(HALO + 31) / 32];
+    __shared__ uint32_t s_dirty[(HALO + 31) / 32];  // a bit per cell whose excess moved in this visit (only it and its neighbours changed)
     __shared__ uint16_t s_slot[kThreads / 64 * kRing];  // per wave: cells of active pixels waiting for a lane
 
     if (tid < 9) s_nb[tid] = 0;
@@ -458,11 +478,11 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
         valid[j] = gx < W && gy < H;
         const int p = min(gy, H - 1) * W + min(gx, W - 1);
-        e[j] = gp(D.e)[p];
+        e[j] = ldc<COH>(&gp(D.e)[p]);
 #pragma unroll
-        for (int k = 0; k < K; ++k) r[j][k] = gp(D.r)[(size_t)k * n + p];
-        rt[j] = gp(D.rt)[p];
-        h[j] = gp(D.h)[p];
+        for (int k = 0; k < K; ++k) r[j][k] = ldc<COH>(&gp(D.r)[(size_t)k * n + p]);
+        rt[j] = ldc<COH>(&gp(D.rt)[p]);
+        h[j] = ldc<COH>(&gp(D.h)[p]);
     }
     // Gap heuristic: no pixel is labelled `gap` (a level that emptied since
     // the last global relabel), so no pixel labelled above it has a residual
@@ -478,7 +498,7 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
     G::ring(min(tid, G::RING - 1), hx, hy);
     const int hc = hy * HW + hx;
     const bool hin = x0 + hx - 1 >= 0 && x0 + hx - 1 < W && y0 + hy - 1 >= 0 && y0 + hy - 1 < H;
-    const int hv = gp(D.h)[min(max(y0 + hy - 1, 0), H - 1) * W + min(max(x0 + hx - 1, 0), W - 1)];
+    const int hv = ldc<COH>(&gp(D.h)[min(max(y0 + hy - 1, 0), H - 1) * W + min(max(x0 + hx - 1, 0), W - 1)]);
     using B = Border<K, TW, TH>;
     constexpr int NBP = (B::E + kThreads - 1) / kThreads;  // inbox words per thread
     GLOBAL int32_t *const inbox = gp(D.inbox) + (size_t)tl * B::E;
@@ -735,13 +755,13 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int r = sh_r[c * K + k];
-            gp(D.r)[(size_t)k * n + p] = r;
+            stc<COH>(&gp(D.r)[(size_t)k * n + p], r);
             if (r > 0) rm |= 1 << k;
         }
-        gp(D.e)[p] = e;
-        gp(D.rt)[p] = rt;
-        gp(D.h)[p] = h;
-        gp(D.rmask)[p] = (uint16_t)rm;
+        stc<COH>(&gp(D.e)[p], e);
+        stc<COH>(&gp(D.rt)[p], rt);
+        stc<COH>(&gp(D.h)[p], h);
+        stc<COH>(&gp(D.rmask)[p], (uint16_t)rm);
     }
     flush_halo();
     // one barrier: the wake-up marks of flush_halo are complete, and the
@@ -766,6 +786,7 @@ __device__ void sweep_tile(const StepParams &P, const InstDesc &D, InstState *S,
 // The nine flags are read unconditionally (a neighbour outside the image
 // reads the clamped, in-image position and is ignored), so that the loads
 // are in flight together.
+template <bool COH>
 __device__ __forceinline__ bool frontier_needs(const InstDesc &D, int tx, int ty, int prev) {
     GLOBAL const uint8_t *chg = gp(D.tile_chg) + (size_t)prev * D.ntiles;
     uint8_t f[9];
@@ -774,7 +795,7 @@ __device__ __forceinline__ bool frontier_needs(const InstDesc &D, int tx, int ty
 #pragma unroll
         for (int dx = -1; dx <= 1; ++dx) {
             const int ntx = min(max(tx + dx, 0), D.tiles_x - 1), nty = min(max(ty + dy, 0), D.tiles_y - 1);
-            f[(dy + 1) * 3 + dx + 1] = chg[nty * D.tiles_x + ntx];
+            f[(dy + 1) * 3 + dx + 1] = ldc<COH>(&chg[nty * D.tiles_x + ntx]);
         }
     bool need = false;
 #pragma unroll
@@ -791,8 +812,8 @@ __device__ __forceinline__ bool frontier_needs(const InstDesc &D, int tx, int ty
 // ---------------------------------------------------------------------------
 // kRelabel: one pass of the exact global relabel (distance to t).
 // ---------------------------------------------------------------------------
-template <int K, int TW, int TH, bool GAP>
-__device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl,
+template <int K, int TW, int TH, bool GAP, bool COH>
+__device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl,
                              int sub, int xrounds, int32_t *lds, int *s_red) {
     using G = Geo<TW, TH>;
     constexpr int PPT = G::PPT, RPI = G::RPI, HW = G::HW;
@@ -818,17 +839,17 @@ __device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
         valid[j] = gx < W && gy < H;
         const int p = min(gy, H - 1) * W + min(gx, W - 1);
-        rm[j] = gp(D.rmask)[p];
-        d[j] = first ? 0 : gp(D.h)[p];
+        rm[j] = ldc<COH>(&gp(D.rmask)[p]);
+        d[j] = first ? 0 : ldc<COH>(&gp(D.h)[p]);
     }
     int hx, hy;
     G::ring(min(tid, G::RING - 1), hx, hy);
     const bool hin = x0 + hx - 1 >= 0 && x0 + hx - 1 < W && y0 + hy - 1 >= 0 && y0 + hy - 1 < H;
     const int hq = min(max(y0 + hy - 1, 0), H - 1) * W + min(max(x0 + hx - 1, 0), W - 1);
-    const int hv = first ? (int)gp(D.rmask)[hq] : gp(D.h)[hq];
+    const int hv = first ? (int)ldc<COH>(&gp(D.rmask)[hq]) : ldc<COH>(&gp(D.h)[hq]);
     // the tile's active count under the previous labels, read now so that
     // the end of the visit does not wait for it
-    const int cnt_prev = (!first && tid == 0) ? gp(D.tile_cnt)[tl] : 0;
+    const int cnt_prev = (!first && tid == 0) ? ldc<COH>(&gp(D.tile_cnt)[tl]) : 0;
     if (first) {
         // fold flow that neighbour tiles pushed into the border pixels (no
         // sweep of this instance runs in the same launch, so nobody else
@@ -838,7 +859,7 @@ __device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *
         GLOBAL int32_t *const inbox = gp(D.inbox) + (size_t)tl * B::E;
         int ibv[NBP];
 #pragma unroll
-        for (int q = 0; q < NBP; ++q) ibv[q] = inbox[min(tid + q * kThreads, B::E - 1)];
+        for (int q = 0; q < NBP; ++q) ibv[q] = ldc<COH>(&inbox[min(tid + q * kThreads, B::E - 1)]);
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
             const int c = (ly0 + j * RPI + 1) * HW + lx + 1;
@@ -854,7 +875,7 @@ __device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *
                 int bx, by, k;
                 B::pair(i, bx, by, k);
                 const int c = (by + 1) * HW + bx + 1;
-                inbox[i] = 0;
+                stc<COH>(&inbox[i], 0);
                 g_add(&gp(D.r)[(size_t)k * n + (y0 + by) * W + x0 + bx], v);
                 atomicAdd(&sh_in[c], v);
                 atomicOr(&sh_ib[c], 1 << k);
@@ -869,7 +890,7 @@ __device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *
                 const int p = (y0 + ly0 + j * RPI) * W + x0 + lx;
                 g_add(&gp(D.e)[p], ein);
                 rm[j] |= (uint32_t)sh_ib[c] | kEBit;
-                gp(D.rmask)[p] = (uint16_t)rm[j];
+                stc<COH>(&gp(D.rmask)[p], (uint16_t)rm[j]);
             }
         }
     }
@@ -1004,7 +1025,7 @@ __device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *
         one[j] = first && d[j] == 1;
         if (gx >= W || gy >= H) continue;
         if (first || d[j] != d0[j]) changed = 1;
-        if (first || d[j] != dpub[j]) gp(D.h)[gy * W + gx] = d[j];
+        if (first || d[j] != dpub[j]) stc<COH>(&gp(D.h)[gy * W + gx], d[j]);
         // gap heuristic: the label histogram follows every change after the
         // first pass (which sets every label to 1 or H_INF and clears it)
         if (GAP && !first && d[j] != d0[j]) {
@@ -1022,12 +1043,12 @@ __device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *
     const int2 vote = block_vote(changed != 0, act, s_red + 8);
     const int tchg = vote.x, tcnt = vote.y;
     if (tid == 0) {
-        gp(D.tile_chg)[(size_t)cur * D.ntiles + tl] = (uint8_t)(tchg ? 1 : 0);
+        stc<COH>(&gp(D.tile_chg)[(size_t)cur * D.ntiles + tl], (uint8_t)(tchg ? 1 : 0));
         const int delta = first ? tcnt : tcnt - cnt_prev;
-        gp(D.tile_cnt)[tl] = tcnt;
+        stc<COH>(&gp(D.tile_cnt)[tl], tcnt);
         if (delta) atomicAdd(&S->active, delta);
         if (tchg) atomicOr(&S->changed, 1);
-        gp(D.tile_act)[tl] = tcnt > 0 ? 1u : 0u;
+        stc<COH>(&gp(D.tile_act)[tl], tcnt > 0 ? 1u : 0u);
     }
 }
 
@@ -1043,8 +1064,8 @@ __device__ void relabel_tile(const StepParams &P, const InstDesc &D, InstState *
 // becomes excess; the preflow stays valid.  The added capacity joins sum cs
 // once this lambda's flow has been taken.
 // ---------------------------------------------------------------------------
-template <int K, int TW, int TH>
-__device__ void cut_tile_swapped(const StepParams &P, const InstDesc &D, InstState *S, int tl, int kk,
+template <int K, int TW, int TH, bool COH>
+__device__ __forceinline__ void cut_tile_swapped(const StepParams &P, const InstDesc &D, InstState *S, int tl, int kk,
                                  int *s_red, unsigned long long *s_sum) {
     using G = Geo<TW, TH>;
     constexpr int PPT = G::PPT, RPI = G::RPI;
@@ -1061,10 +1082,10 @@ __device__ void cut_tile_swapped(const StepParams &P, const InstDesc &D, InstSta
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
         valid[j] = gx < W && gy < H;
         const int p = min(gy, H - 1) * W + min(gx, W - 1);
-        hv[j] = gp(D.h)[p];
-        rmv[j] = gp(D.rmask)[p];
-        ev[j] = gp(D.e)[p];
-        rtv[j] = gp(D.rt)[p];
+        hv[j] = ldc<COH>(&gp(D.h)[p]);
+        rmv[j] = ldc<COH>(&gp(D.rmask)[p]);
+        ev[j] = ldc<COH>(&gp(D.e)[p]);
+        rtv[j] = ldc<COH>(&gp(D.rt)[p]);
         sdv[j] = 0;
         slv[j] = 1;
         if (dlam > 0) {
@@ -1078,7 +1099,7 @@ __device__ void cut_tile_swapped(const StepParams &P, const InstDesc &D, InstSta
     for (int j = 0; j < PPT; ++j) {
         if (!valid[j]) continue;
         const int p = (y0 + ly0 + j * RPI) * W + x0 + lx;
-        mask[p] = hv[j] < kHInf ? 1 : 0;
+        mask[p] = hv[j] < kHInf ? 1 : 0;  // not read again by this launch
         if (rmv[j] & kEBit) se += ev[j];
         const int sl = sdv[j] == 0 ? slv[j] : 0;
         if (dlam > 0 && sl > 0) {
@@ -1086,10 +1107,10 @@ __device__ void cut_tile_swapped(const StepParams &P, const InstDesc &D, InstSta
             sraise += inc;
             const int d = inc < rtv[j] ? inc : rtv[j];
             const int nrt = rtv[j] - d, ne = ev[j] + (inc - d);
-            gp(D.rt)[p] = nrt;
-            gp(D.e)[p] = ne;
+            stc<COH>(&gp(D.rt)[p], nrt);
+            stc<COH>(&gp(D.e)[p], ne);
             const int rm = (rmv[j] & ~(kRtBit | kEBit)) | (nrt > 0 ? kRtBit : 0) | (ne > 0 ? kEBit : 0);
-            if (rm != rmv[j]) gp(D.rmask)[p] = (uint16_t)rm;
+            if (rm != rmv[j]) stc<COH>(&gp(D.rmask)[p], (uint16_t)rm);
             act |= ne > 0 && hv[j] < kHInf;
         }
     }
@@ -1102,7 +1123,7 @@ __device__ void cut_tile_swapped(const StepParams &P, const InstDesc &D, InstSta
     const int tact = block_any(act != 0, s_red + 28) ? 1 : 0;
     if (tid == 0) {
         if (tact) g_or(&gp(D.tile_act)[tl], 1u);
-        gp(D.tile_chg)[tl] = 0;  // the cut is complete after this pass
+        stc<COH>(&gp(D.tile_chg)[tl], (uint8_t)0);  // the cut is complete after this pass
         if (tse) atomicAdd((unsigned long long *)&S->sum_e, (unsigned long long)tse);
         if (tra) atomicAdd((unsigned long long *)&S->sum_raise, (unsigned long long)tra);
     }
@@ -1114,8 +1135,8 @@ __device__ void cut_tile_swapped(const StepParams &P, const InstDesc &D, InstSta
 // The first pass also sums the excess (for F) and raises the sink residuals
 // to the next lambda (warm start).
 // ---------------------------------------------------------------------------
-template <int K, int TW, int TH>
-__device__ void cut_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl, int sub,
+template <int K, int TW, int TH, bool COH>
+__device__ __forceinline__ void cut_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl, int sub,
                          int kk, int xrounds, int32_t *lds, int *s_red, unsigned long long *s_sum) {
     using G = Geo<TW, TH>;
     constexpr int PPT = G::PPT, RPI = G::RPI, HW = G::HW;
@@ -1141,27 +1162,27 @@ __device__ void cut_tile(const StepParams &P, const InstDesc &D, InstState *S, i
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
         valid[j] = gx < W && gy < H;
         const int p = min(gy, H - 1) * W + min(gx, W - 1);
-        rmv[j] = gp(D.rmask)[p];
+        rmv[j] = ldc<COH>(&gp(D.rmask)[p]);
         m[j] = 0;
         ev[j] = rtv[j] = sdv[j] = 0;
         slv[j] = 1;
         if (first) {
-            ev[j] = gp(D.e)[p];
+            ev[j] = ldc<COH>(&gp(D.e)[p]);
             if (dlam > 0) {
-                rtv[j] = gp(D.rt)[p];
+                rtv[j] = ldc<COH>(&gp(D.rt)[p]);
                 if (D.seed) sdv[j] = gp(D.seed)[p];
                 if (D.slope) slv[j] = gp(D.slope)[p];
             }
         } else {
-            m[j] = mask[p];
+            m[j] = ldc<COH>(&mask[p]);
         }
     }
     int hx, hy;
     G::ring(min(tid, G::RING - 1), hx, hy);
     const bool hin = x0 + hx - 1 >= 0 && x0 + hx - 1 < W && y0 + hy - 1 >= 0 && y0 + hy - 1 < H;
     const int hq = min(max(y0 + hy - 1, 0), H - 1) * W + min(max(x0 + hx - 1, 0), W - 1);
-    const int hrm = gp(D.rmask)[hq];
-    const int hmk = first ? ((hrm & kEBit) ? 1 : 0) : mask[hq];
+    const int hrm = ldc<COH>(&gp(D.rmask)[hq]);
+    const int hmk = first ? ((hrm & kEBit) ? 1 : 0) : ldc<COH>(&mask[hq]);
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         if (!valid[j]) {
@@ -1175,8 +1196,8 @@ __device__ void cut_tile(const StepParams &P, const InstDesc &D, InstState *S, i
             if (dlam > 0 && sl > 0) {
                 const int p = (y0 + ly0 + j * RPI) * W + x0 + lx;
                 const int nrt = rtv[j] + sl * dlam;
-                gp(D.rt)[p] = nrt;
-                if (nrt > 0 && !(rmv[j] & kRtBit)) gp(D.rmask)[p] = (uint16_t)(rmv[j] | kRtBit);
+                stc<COH>(&gp(D.rt)[p], nrt);
+                if (nrt > 0 && !(rmv[j] & kRtBit)) stc<COH>(&gp(D.rmask)[p], (uint16_t)(rmv[j] | kRtBit));
             }
         }
         m0[j] = m[j];
@@ -1253,35 +1274,27 @@ __device__ void cut_tile(const StepParams &P, const InstDesc &D, InstState *S, i
         const int gx = x0 + lx, gy = y0 + ly;
         if (gx >= W || gy >= H) continue;
         if (first || m[j] != m0[j]) changed = 1;
-        if (first || m[j] != mpub[j]) mask[gy * W + gx] = (uint8_t)m[j];
+        if (first || m[j] != mpub[j]) stc<COH>(&mask[gy * W + gx], (uint8_t)m[j]);
     }
     const int tchg = block_any(changed != 0, s_red + 28) ? 1 : 0;
     long long tse = 0;
     if (first) tse = block_sum_i64(se, s_sum);
     if (tid == 0) {
-        gp(D.tile_chg)[(size_t)cur * D.ntiles + tl] = (uint8_t)(tchg ? 1 : 0);
+        stc<COH>(&gp(D.tile_chg)[(size_t)cur * D.ntiles + tl], (uint8_t)(tchg ? 1 : 0));
         if (tchg) atomicOr(&S->changed, 1);
         if (tse) atomicAdd((unsigned long long *)&S->sum_e, (unsigned long long)tse);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Phase machine of every instance of the work list (one thread each), run
-// after the tile work of every superstep.
+// Phase machine of an instance, run by one thread after the tile work of each
+// of its supersteps.  Returns whether the instance is still running.
 // ---------------------------------------------------------------------------
-// Returns whether the instance is still running afterwards.
-__device__ bool control_one(const StepParams &P, int w) {
-    const int i = P.wl_ident ? w : P.wl_slot[w];
-    // The state and the descriptor fields used here are read in one batch:
-    // this kernel runs alone after the tile kernels of the superstep, whose
-    // writes it sees at the launch boundary.
-    InstState S = P.st[i];
-    const InstDesc *Dp = &P.desc[i];
+__device__ __forceinline__ bool control_state(const StepParams &P, int i, const InstDesc *Dp, InstState &S) {
     const int L = Dp->L;
     int64_t *flows = Dp->flows;
     int32_t *status_out = Dp->status;
     int ph = S.phase;
-    if (ph == kIdle || ph == kDone) return false;
     S.steps += 1;
     bool done = false;
     int status = PMF_OK;
@@ -1380,8 +1393,18 @@ __device__ bool control_one(const StepParams &P, int w) {
         P.ring[at % P.ring_cap] = i;
     }
     S.phase = ph;
-    P.st[i] = S;
     return ph != kDone;
+}
+
+__device__ bool control_one(const StepParams &P, int w) {
+    const int i = P.wl_ident ? w : P.wl_slot[w];
+    // The state is read in one batch: this kernel runs alone after the tile
+    // kernels of the superstep, whose writes it sees at the launch boundary.
+    InstState S = P.st[i];
+    if (S.phase == kIdle || S.phase == kDone) return false;
+    const bool run = control_state(P, i, &P.desc[i], S);
+    P.st[i] = S;
+    return run;
 }
 
 // Append `value` to `list` for every lane whose `want` is set: one atomic per
@@ -1437,7 +1460,7 @@ __device__ void compact_instance(const StepParams &P, int w) {
                 bf = true;
             } else {
                 const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
-                bf = frontier_needs(D, tx, ty, (sub & 1) ^ 1);
+                bf = frontier_needs<false>(D, tx, ty, (sub & 1) ^ 1);
                 if (!bf) gp(D.tile_chg)[(size_t)(sub & 1) * D.ntiles + tl] = 0;
             }
         }
@@ -1522,7 +1545,7 @@ __device__ void tile_work(const StepParams &P, int ws, int wp, int32_t *lds, int
         if (i < s_n) {
             const int2 en = list_item(P, ws, s_lo + i);
             const InstDesc D = load_desc(P.desc, en.x);
-            sweep_tile<K, TW, TH, GAP>(P, D, &P.st[en.x], en.y, iters, xsw, lds, s_red);
+            sweep_tile<K, TW, TH, GAP, false>(P, D, &P.st[en.x], en.y, iters, xsw, lds, s_red);
         } else {
             const int2 en = list_item(P, wp, p_lo + i - s_n);
             InstState *S = &P.st[en.x];
@@ -1530,15 +1553,15 @@ __device__ void tile_work(const StepParams &P, int ws, int wp, int32_t *lds, int
             const InstDesc D = load_desc(P.desc, en.x);
             const int tl = en.y;
             if (phase == kInit)
-                init_tile<K, TW, TH>(P, D, S, tl, s_red, s_sum);
+                init_tile<K, TW, TH, false>(P, D, S, tl, swap != 0, s_red, s_sum);
             else if (phase == kOrient)
                 orient_tile<K, TW, TH>(P, D, S, tl, s_red);
             else if (phase == kRelabel)
-                relabel_tile<K, TW, TH, GAP>(P, D, S, tl, sub, xrounds, lds, s_red);
+                relabel_tile<K, TW, TH, GAP, false>(P, D, S, tl, sub, xrounds, lds, s_red);
             else if (swap)
-                cut_tile_swapped<K, TW, TH>(P, D, S, tl, kk, s_red, s_sum);
+                cut_tile_swapped<K, TW, TH, false>(P, D, S, tl, kk, s_red, s_sum);
             else
-                cut_tile<K, TW, TH>(P, D, S, tl, sub, kk, xrounds, lds, s_red, s_sum);
+                cut_tile<K, TW, TH, false>(P, D, S, tl, sub, kk, xrounds, lds, s_red, s_sum);
         }
     }
 }
@@ -1720,6 +1743,429 @@ __global__ __launch_bounds__(kThreads) void k_persist(const StepParams *Pg, int 
     }
 }
 
+// ---------------------------------------------------------------------------
+// The device-driven solve.  Every instance runs its own supersteps, with no
+// launch boundary and no other instance to wait for: the tiles listed for an
+// instance's superstep are claimed one by one by whichever workgroups are
+// free, and the workgroup that completes the last of them runs the
+// instance's phase machine, lists the tiles of its next superstep and
+// publishes them.
+//
+// Per instance, three cache lines (EngineParams::sync) and a tile list (its
+// share of the list memory):
+//   claim  {count | superstep tag | batch, next}: one 64-bit add claims the
+//          next `batch` entries of the tile list
+//   done   entries completed; the add that reaches count is the last
+//   info   what the superstep does (phase, pass number, lambda, iterations)
+// Per launch, one copy per XCD (polled by its own workgroups only): a bit per
+// instance that has entries nobody has claimed yet, and the number of tiles
+// of the instances still running.
+//
+// Nothing waits for a particular workgroup: a published superstep is claimed
+// by its publisher if by nobody else, so the launch ends whatever the number
+// of workgroups the device holds at once; a workgroup with nothing to claim
+// polls until no instance runs (or gives up after kEngIdleTicks).
+//
+// Everything that crosses workgroups goes through agent-scope accesses
+// (COH); a workgroup's stores are complete (stores_done in every wave, then
+// the workgroup barrier) before the atomic or the store that lets another
+// workgroup read them is issued.
+// ---------------------------------------------------------------------------
+constexpr int kEngReplicas = 8;                  // one copy of the bits and the count per XCD
+constexpr long long kEngIdleTicks = 200000000;   // 2 s of the 100 MHz constant clock
+constexpr int kEngBatch = 16;
+
+// the high word of claim
+constexpr int kClCountBits = 20;
+__device__ __forceinline__ uint32_t claim_hi(int count, int tag, int batch) {
+    return (uint32_t)count | ((uint32_t)(tag & 255) << kClCountBits) | ((uint32_t)(batch - 1) << 28);
+}
+__device__ __forceinline__ int claim_count(uint32_t hi) { return (int)(hi & ((1u << kClCountBits) - 1)); }
+__device__ __forceinline__ int claim_batch(uint32_t hi) { return (int)(hi >> 28) + 1; }
+
+// a workgroup's task, in LDS
+struct EngTask {
+    int w, slot, first, n;  // entries [first, first + n) of the list of instance w; n = 0: leave
+    uint32_t hi;            // the claim word they came from
+    int info[kEngInfo];     // kInPhase ...
+    int last;
+    int tile[kEngBatch];
+};
+
+__device__ __forceinline__ int xcc_id() {
+    // HW_REG_XCC_ID (20), all 32 bits
+    return (int)(__builtin_amdgcn_s_getreg((31 << 11) | 20) & (kEngReplicas - 1));
+}
+
+// Set or clear instance w's bit in every copy (the first kEngReplicas lanes of a wave).
+__device__ __forceinline__ void eng_mark(const EngineParams &E, int w, bool on) {
+    const int lane = (int)(threadIdx.x & 63);
+    if (lane < kEngReplicas) {
+        GLOBAL unsigned long long *p = gp(E.avail) + (size_t)lane * E.avail_words + (w >> 6);
+        const unsigned long long b = 1ull << (w & 63);
+        if (on)
+            g_or(p, b);
+        else
+            g_and(p, ~b);
+    }
+}
+
+// d tiles more (or fewer) belong to instances that are running.
+__device__ __forceinline__ void eng_live(const EngineParams &E, int d) {
+    if (threadIdx.x < kEngReplicas) g_add(gp(E.live) + threadIdx.x * 32, d);
+}
+
+// The first wave takes the entries that a claim (`hi`, `next`) returned,
+// clearing the instance's bit with the last of them; false when none were
+// left.  pre: list entry pre_first + lane of the same superstep, if pre_hi == hi.
+__device__ __forceinline__ bool eng_take(const StepParams &P, const EngineParams &E, int w, int slot, uint32_t hi,
+                                         int next, uint32_t pre_hi, int pre_first, int pre, EngTask *T) {
+    const int lane = (int)(threadIdx.x & 63);
+    const int count = claim_count(hi), batch = claim_batch(hi);
+    if (next >= count) return false;
+    if (next + batch >= count) eng_mark(E, w, false);
+    const int n = imin(batch, count - next);
+    const int at = next - pre_first;
+    if (pre_hi == hi && at >= 0 && at + n <= 64) {
+        if (lane >= at && lane < at + n) T->tile[lane - at] = pre;
+    } else {
+        GLOBAL const int32_t *list = gp(P.lists) + (size_t)desc_word(P.desc, slot, &InstDesc::tile0) * kEngLine;
+        if (lane < n) T->tile[lane] = ld_agent(&list[next + lane]);
+    }
+    // what the superstep does (the claim has returned)
+    if (pre_hi != hi && lane < kEngInfo) T->info[lane] = ld_agent(gp(E.sync) + (size_t)w * kEngSync + kSyInfo + lane);
+    if (lane == 0) {
+        T->w = w;
+        T->slot = slot;
+        T->first = next;
+        T->n = n;
+        T->hi = hi;
+    }
+    return true;
+}
+
+// First wave of a workgroup without a task: look for an instance with
+// unclaimed entries, starting at a random one of them, until something is
+// claimed (true) or there is nothing left for this workgroup (false): no
+// instance runs, or the workgroups before this one are enough for those that
+// do (half as many as they have tiles: a superstep rarely lists more).
+// Polling is not free: it loads the lines that publishing and claiming wait
+// for.  25 seeds x 20 lambdas of 500 x 375: 26.0 ms with a poll every 0.5 us
+// and a workgroup per tile, 25.3 with 1.8 us, 25.1 with half the workgroups.
+__device__ __forceinline__ bool eng_find(const StepParams &P, const EngineParams &E, int xcc, uint32_t &rnd,
+                                         EngTask *T) {
+    const int lane = (int)(threadIdx.x & 63);
+    const int nseg = (E.avail_words + 63) >> 6;
+    int seg = nseg > 1 ? (int)(blockIdx.x % (unsigned)nseg) : 0;
+    GLOBAL const unsigned long long *avail = gp(E.avail) + (size_t)xcc * E.avail_words;
+    const long long t0 = wall_clock64();
+    unsigned tries = 0;
+    while (wall_clock64() - t0 < kEngIdleTicks) {
+        unsigned long long word = 0;
+        if (seg * 64 + lane < E.avail_words) word = ld_agent(&avail[seg * 64 + lane]);
+        const int live = ld_agent(gp(E.live) + xcc * 32);
+        if ((int)blockIdx.x >= (live > 0 ? live / 2 + 32 : 0)) return false;
+        const int c = bits(word);
+        int pre = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int t = __shfl_up(pre, off);
+            if (lane >= off) pre += t;
+        }
+        const int total = __builtin_amdgcn_readlane(pre, 63);
+        const unsigned wgs = (unsigned)imin((int)gridDim.x, live / 2 + 32);
+        rnd = rnd * 1664525u + 1013904223u;
+        // Few instances and many idle workgroups: only some 64 per instance
+        // look at its claim word (the others would queue up at it), twice as
+        // many with every try.
+        if (total == 0 || (unsigned long long)(rnd >> 16) * wgs > (((unsigned long long)(64u * total) << imin((int)tries, 10)) << 16)) {
+            if (total == 0)
+                __builtin_amdgcn_s_sleep(64);
+            else
+                ++tries;
+            seg = seg + 1 < nseg ? seg + 1 : 0;
+            continue;
+        }
+        rnd = rnd * 1664525u + 1013904223u;
+        const int r = (int)(((unsigned long long)rnd * (unsigned)total) >> 32);
+        const int owner = __ffsll((long long)__ballot(pre > r)) - 1;
+        unsigned long long x = word;
+        int bit = 0;
+        if (lane == owner) {
+            for (int k = r - (pre - c); k > 0; --k) x &= x - 1;
+            bit = __ffsll((long long)x) - 1;
+        }
+        const int w = (seg * 64 + owner) * 64 + __builtin_amdgcn_readlane(bit, owner);
+        const int slot = P.wl_ident ? w : __builtin_amdgcn_readfirstlane(P.wl_slot[w]);
+        GLOBAL unsigned long long *claim = (GLOBAL unsigned long long *)(gp(E.sync) + (size_t)w * kEngSync + kSyClaim);
+        // likewise about twice as many as there are entries claim
+        const unsigned long long seen = ld_agent(claim);
+        const int left = claim_count((uint32_t)(seen >> 32)) - (int)(uint32_t)seen;
+        ++tries;
+        if (left <= 0 || (unsigned long long)(rnd & 0xffffu) * wgs >
+                             (((unsigned long long)((2u * left + 1) * total) << imin((int)tries, 10)) << 16)) {
+            __builtin_amdgcn_s_sleep(4);
+            continue;
+        }
+        unsigned long long old = 0;
+        if (lane == 0)
+            old = __hip_atomic_fetch_add(claim, (unsigned long long)claim_batch((uint32_t)(seen >> 32)),
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(old >> 32));
+        const int next = __builtin_amdgcn_readfirstlane((int)(uint32_t)old);
+        if (eng_take(P, E, w, slot, hi, next, 0u, 0, 0, T)) return true;
+    }
+    return false;
+}
+
+// The end of an instance's superstep (finished: T holds its last task) or the
+// start of a launch: phase machine, then the tiles of the next superstep,
+// listed as compact_instance does; a superstep without tiles is over at once.
+// With `take` the first entries become the calling workgroup's task.  Returns
+// false when the instance has nothing more to do in this launch.
+__device__ __forceinline__ bool eng_advance(const StepParams &P, const EngineParams &E, const InstDesc &D, int w,
+                                            int slot, bool finished, bool take, int32_t *lds, int *s_red,
+                                            EngTask *T) {
+    constexpr int NW = (int)(sizeof(InstState) / 4);
+    static_assert(NW + 2 <= kThreads, "state read by one word per thread");
+    const int tid = thread_id();
+    GLOBAL int32_t *sy = gp(E.sync) + (size_t)w * kEngSync;
+    GLOBAL int32_t *list = gp(P.lists) + (size_t)D.tile0 * kEngLine;
+    GLOBAL int32_t *st = (GLOBAL int32_t *)&P.st[slot];
+    InstState &S = *reinterpret_cast<InstState *>(lds);
+    int32_t *s_left = lds + NW;   // supersteps the instance may still run in this launch
+    int32_t *s_live = lds + NW + 1;
+    // the flags that the next listing may need, read along with the state:
+    // nobody changes them until it is published
+    uint32_t act0 = 0;
+    bool need0 = false;
+    const bool ahead = finished;
+    if (ahead && tid < D.ntiles) {
+        act0 = ld_agent(&gp(D.tile_act)[tid]);
+        need0 = frontier_needs<true>(D, tid % D.tiles_x, tid / D.tiles_x, T->info[kInSub] & 1);
+    }
+    __syncthreads();  // the tile work has left the LDS
+    if (tid < NW) lds[tid] = ld_agent(&st[tid]);
+    if (tid == NW) *s_left = finished ? T->info[kInLeft] : E.quota;
+    if (tid == NW + 1) *s_live = ld_agent(gp(E.live));
+    __syncthreads();
+    const int tw = D.tile_w, th = (kThreads * 4) / tw;
+    int count = 0, px = 0, phase = 0, sub = 0;
+    for (;;) {
+        if (tid == 0) {
+            int go;
+            if (finished) {
+                const bool run = control_state(P, slot, &D, S);
+                *s_left -= 1;
+                go = run && *s_left > 0;
+            } else {
+                go = S.phase != kIdle && S.phase != kDone;
+            }
+            s_red[0] = go;
+        }
+        __syncthreads();
+        const int go = s_red[0];
+        if (!go) break;
+        phase = __builtin_amdgcn_readfirstlane(S.phase);
+        sub = __builtin_amdgcn_readfirstlane(S.sub);
+        count = 0;
+        px = 0;
+        for (int t0 = 0; t0 < D.ntiles; t0 += kThreads) {
+            const int tl = t0 + tid;
+            bool want = false;
+            const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
+            if (tl < D.ntiles) {
+                if (phase == kSweep) {
+                    want = ((ahead && t0 == 0 ? act0 : ld_agent(&gp(D.tile_act)[tl])) & 3u) != 0u;
+                } else if (phase == kInit || phase == kOrient || sub == 0) {
+                    want = true;
+                } else {
+                    want = ahead && t0 == 0 ? need0 : frontier_needs<true>(D, tx, ty, (sub & 1) ^ 1);
+                    if (!want) st_agent(&gp(D.tile_chg)[(size_t)(sub & 1) * D.ntiles + tl], (uint8_t)0);
+                }
+            }
+            const unsigned long long m = __ballot(want);
+            int v = want ? tile_pixels(D.W, D.H, tw, th, tx * tw, ty * th) : 0;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+            const int wv = tid >> 6;
+            if ((tid & 63) == 0) {
+                s_red[8 + 2 * wv] = bits(m);
+                s_red[9 + 2 * wv] = v;
+            }
+            __syncthreads();
+            int at = count + prefix_count(m);
+#pragma unroll
+            for (int i = 0; i < kThreads / 64; ++i) {
+                if (i < wv) at += s_red[8 + 2 * i];
+                count += s_red[8 + 2 * i];
+                px += s_red[9 + 2 * i];
+            }
+            if (want) {
+                st_agent(&list[at], tl);
+                if (at < kEngBatch) T->tile[at] = tl;
+            }
+            __syncthreads();
+        }
+        if (tid == 0) S.listed = phase == kSweep && count > 0 ? 1 : 0;
+        if (count > 0) break;
+        finished = true;  // the control of an empty superstep
+        __syncthreads();
+    }
+    count = __builtin_amdgcn_readfirstlane(count);
+    if (tid == 0 && px > 0) {
+        const bool x = S.swap != 0;
+        int64_t *ctr = phase == kSweep     ? &S.px_sweep
+                       : phase == kRelabel ? &S.px_relabel
+                       : phase == kOrient  ? &S.px_orient
+                       : phase == kInit    ? (x ? &S.px_init_x : &S.px_init)
+                                           : (x ? &S.px_cut_x : &S.px_cut);
+        *ctr += px;
+    }
+    __syncthreads();
+    if (tid < NW) st_agent(&st[tid], lds[tid]);
+    if (count == 0) {
+        if (tid == 0) atomicMax(E.rounds, E.quota - *s_left);
+        return false;
+    }
+    // an instance with few tiles, next to few others, is latency bound: its
+    // visits may run longer at no cost in width
+    const bool brief = (long long)count * (*s_live > D.ntiles ? *s_live : D.ntiles) < (long long)P.tail_tiles * D.ntiles;
+    const int batch = imin((count >> 9) + 1, kEngBatch);
+    const uint32_t hi = claim_hi(count, *s_left, batch);
+    const int own = take ? imin(batch, count) : 0;
+    if (tid < kEngInfo) {
+        const int v = tid == kInPhase  ? phase
+                      : tid == kInSwap ? S.swap
+                      : tid == kInSub  ? sub
+                      : tid == kInK    ? S.k
+                      : tid == kInReps ? (phase == kSweep ? (brief ? P.tail_inner_iters : P.inner_iters)
+                                                          : (brief ? P.tail_exchange_rounds : P.exchange_rounds))
+                      : tid == kInXsw  ? (brief ? P.tail_sweep_exchanges : 0)
+                                       : *s_left;
+        st_agent(&sy[kSyInfo + tid], v);
+        T->info[tid] = v;
+    }
+    if (tid == 0) __hip_atomic_store((GLOBAL unsigned long long *)(sy + kSyDone), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the bit goes up before the claim word: the last claimer of this
+    // superstep clears it, and must not do so before it is set
+    if (tid < 64 && count > own) eng_mark(E, w, true);
+    stores_done();
+    __syncthreads();
+    if (tid == 0) {
+        __hip_atomic_store((GLOBAL unsigned long long *)(sy + kSyClaim),
+                           ((unsigned long long)hi << 32) | (unsigned)own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        T->w = w;
+        T->slot = slot;
+        T->first = 0;
+        T->n = own;
+        T->hi = hi;
+    }
+    return true;
+}
+
+// Start of a launch: one workgroup per instance of the work list publishes
+// its current superstep (the copies of the bits and counts were zeroed before).
+__global__ __launch_bounds__(kThreads) void k_engine_start(StepParams P, EngineParams E) {
+    __shared__ int32_t lds[kThreads];
+    __shared__ int s_red[32];
+    __shared__ EngTask s_task;
+    const int w = (int)blockIdx.x;
+    const int slot = P.wl_ident ? w : __builtin_amdgcn_readfirstlane(P.wl_slot[w]);
+    const InstDesc D = load_desc(P.desc, slot);
+    if (eng_advance(P, E, D, w, slot, false, false, lds, s_red, &s_task)) eng_live(E, D.ntiles);
+}
+
+template <int KSET, int TW, int TH>
+__global__ __launch_bounds__(kThreads, KSET == 4 ? 4 : 3) void k_engine(StepParams P, EngineParams E) {
+    constexpr int KM = KSET == 4 ? 4 : 8;
+    __shared__ int32_t lds[(3 + KM) * (TW + 2) * (TH + 2)];  // sweep layout; passes use 4 planes
+    __shared__ int s_red[32];  // [0]: block_count_ballot, [8..15]: block_vote, [16..31]: block_any
+    __shared__ unsigned long long s_sum;
+    __shared__ EngTask s_task;
+    const int xcc = xcc_id();
+    uint32_t rnd = (blockIdx.x + 1u) * 2654435761u;
+    bool have = false;
+    for (;;) {
+        const int tid = thread_id(), lane = tid & 63;
+        if (!have && tid < 64) {
+            const bool got = eng_find(P, E, xcc, rnd, &s_task);
+            if (!got && lane == 0) s_task.n = 0;
+        }
+        __syncthreads();
+        const int n = __builtin_amdgcn_readfirstlane(s_task.n);
+        if (n == 0) return;
+        const int slot = __builtin_amdgcn_readfirstlane(s_task.slot);
+        const int phase = __builtin_amdgcn_readfirstlane(s_task.info[kInPhase]);
+        const int swap = __builtin_amdgcn_readfirstlane(s_task.info[kInSwap]);
+        const int sub = __builtin_amdgcn_readfirstlane(s_task.info[kInSub]);
+        const int kk = __builtin_amdgcn_readfirstlane(s_task.info[kInK]);
+        const int reps = __builtin_amdgcn_readfirstlane(s_task.info[kInReps]);
+        const int xsw = __builtin_amdgcn_readfirstlane(s_task.info[kInXsw]);
+        auto visit = [&](auto kc, int tl) {
+            constexpr int K = decltype(kc)::value;
+            InstState *S = &P.st[slot];
+            const InstDesc D = load_desc(P.desc, slot);
+            if (phase == kSweep)
+                sweep_tile<K, TW, TH, false, true>(P, D, S, tl, reps, xsw, lds, s_red);
+            else if (phase == kRelabel)
+                relabel_tile<K, TW, TH, false, true>(P, D, S, tl, sub, reps, lds, s_red);
+            else if (phase == kCut && swap)
+                cut_tile_swapped<K, TW, TH, true>(P, D, S, tl, kk, s_red, &s_sum);
+            else if (phase == kCut)
+                cut_tile<K, TW, TH, true>(P, D, S, tl, sub, kk, reps, lds, s_red, &s_sum);
+            else if (phase == kInit)
+                init_tile<K, TW, TH, true>(P, D, S, tl, swap != 0, s_red, &s_sum);
+            else
+                orient_tile<K, TW, TH>(P, D, S, tl, s_red);
+        };
+        for (int i = 0; i < n; ++i) {
+            const int tl = __builtin_amdgcn_readfirstlane(s_task.tile[i]);
+            if (i > 0) __syncthreads();  // the previous tile's LDS is no longer in use
+            if constexpr (KSET != 8) {
+                if (KSET == 4 || desc_word(P.desc, slot, &InstDesc::K) == 4) visit(std::integral_constant<int, 4>(), tl);
+            }
+            if constexpr (KSET != 4) {
+                if (KSET == 8 || desc_word(P.desc, slot, &InstDesc::K) == 8) visit(std::integral_constant<int, 8>(), tl);
+            }
+        }
+        stores_done();
+        __syncthreads();
+        const int w = __builtin_amdgcn_readfirstlane(s_task.w);
+        if (tid < 64) {
+            // completed entries counted and the next ones claimed side by
+            // side, with the list entries that the claim will most likely bring
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_task.hi);
+            const int first = __builtin_amdgcn_readfirstlane(s_task.first);
+            GLOBAL const int32_t *list = gp(P.lists) + (size_t)desc_word(P.desc, slot, &InstDesc::tile0) * kEngLine;
+            unsigned long long old = 0;
+            if (lane < 2) {
+                GLOBAL unsigned long long *p =
+                    (GLOBAL unsigned long long *)(gp(E.sync) + (size_t)w * kEngSync + (lane == 0 ? kSyDone : kSyClaim));
+                old = __hip_atomic_fetch_add(p, (unsigned long long)(lane == 0 ? n : claim_batch(hi)), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+            }
+            const int pre = ld_agent(&list[imin(first + lane, claim_count(hi) - 1)]);
+            const int done = __builtin_amdgcn_readfirstlane((int)(uint32_t)old) + n;
+            const uint32_t nhi = (uint32_t)__builtin_amdgcn_readlane((int)(old >> 32), 1);
+            const int next = __builtin_amdgcn_readlane((int)(uint32_t)old, 1);
+            // (the superstep may have been completed by others and the
+            // instance's next one published in between: its tag differs)
+            const bool last = done == claim_count(hi);
+            const bool more = !last && eng_take(P, E, w, slot, nhi, next, hi, first, pre, &s_task);
+            if (lane == 0) s_task.last = last ? 2 : more ? 1 : 0;
+        }
+        __syncthreads();
+        const int last = __builtin_amdgcn_readfirstlane(s_task.last);
+        have = last == 1;
+        if (last == 2) {
+            const InstDesc D = load_desc(P.desc, slot);
+            have = eng_advance(P, E, D, w, slot, true, true, lds, s_red, &s_task);
+            if (!have) eng_live(E, -D.ntiles);
+        }
+    }
+}
+
 // Nested masks to one byte per pixel: the number of lambdas whose minimal
 // source side holds the pixel (the sets shrink as lambda grows, so mask k is
 // level > k).
@@ -1883,6 +2329,36 @@ int launch_persist(const StepParams *p_dev, int tile_w, int kset, int grid, int 
         return -1;
     }
     return 0;
+}
+
+template <int TW, int TH>
+static const void *engine_fn(int kset) {
+    return kset == 4 ? (const void *)k_engine<4, TW, TH>
+                     : kset == 8 ? (const void *)k_engine<8, TW, TH> : (const void *)k_engine<12, TW, TH>;
+}
+
+int engine_workgroups(int tile_w, int kset) {
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    const void *fn = tile_w == 64 ? engine_fn<64, 16>(kset) : engine_fn<32, 32>(kset);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, fn, kThreads, 0) != hipSuccess) return 0;
+    return per * cus;
+}
+
+int launch_engine(const StepParams &p, const EngineParams &e, int tile_w, int kset, int grid, void *stream) {
+    if (grid < 1 || p.nwl < 1 || p.nwl > 64 * e.avail_words) return -1;
+    hipStream_t s = (hipStream_t)stream;
+    if (hipMemsetAsync(e.live, 0, engine_clear_bytes(e.avail_words), s) != hipSuccess) return -1;
+    hipLaunchKernelGGL(k_engine_start, dim3(p.nwl), dim3(kThreads), 0, s, p, e);
+    const void *fn = tile_w == 64 ? engine_fn<64, 16>(kset) : engine_fn<32, 32>(kset);
+    void *args[] = {(void *)&p, (void *)&e};
+    if (hipLaunchKernel(fn, dim3(grid), dim3(kThreads), args, 0, s) != hipSuccess) {
+        (void)hipGetLastError();
+        return -1;
+    }
+    return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
 int launch_superstep(const StepParams &p, int tile_w, void *stream, void *const *events, bool split) {
