@@ -68,7 +68,7 @@ int check_instance(const pmf_instance &I) {
 
 // Byte offsets of one instance's planes inside its block.
 struct BlockLayout {
-    size_t r, e, rt, h, inbox, rmask, masks, tile_act, tile_chg, tile_cnt, hist, total;
+    size_t r, e, h, inbox, rmask, masks, tile_act, tile_chg, tile_cnt, hist, total;
     int tiles_x, tiles_y;
 };
 
@@ -85,7 +85,7 @@ BlockLayout block_layout(const pmf_instance &I, int tw, int th, bool gap) {
     };
     b.r = take(4 * K * px);
     b.e = take(4 * px);
-    b.rt = take(4 * px);
+    take(4 * px);
     b.h = take(4 * px);
     b.inbox = take(4 * nt * (size_t)border_words(I.K, tw, th));
     b.rmask = take(2 * px);
@@ -508,7 +508,6 @@ int submit(pmf_handle *h, const pmf_instance *inst, int n, int64_t *flows_out, i
         D.seed = I.seed;
         D.r = (int32_t *)(base + B.r);
         D.e = (int32_t *)(base + B.e);
-        D.rt = (int32_t *)(base + B.rt);
         D.h = (int32_t *)(base + B.h);
         D.inbox = (int32_t *)(base + B.inbox);
         D.rmask = (uint16_t *)(base + B.rmask);
@@ -1024,7 +1023,7 @@ int64_t batch_tiles(const pmf_instance *inst, int n, int C, int tw, int th, int6
 int longest_parallel_chunk(pmf_handle *h, const pmf_instance *inst, int n, int C, int maxL) {
     int64_t t8 = 0;
     const int64_t t = batch_tiles(inst, n, 1, h->tw, h->th, &t8);
-    const int res = resident_workgroups(2 * t8 >= t ? 8 : 4, h->tw);
+    const int res = engine_workgroups(h->tw, 2 * t8 >= t ? 8 : 4);
     if (res <= 0) return C;
     const int64_t target = kTilesPerWorkgroup * res;
     while (C < maxL && batch_tiles(inst, n, C + 1, h->tw, h->th, nullptr) >= target) ++C;

@@ -2,14 +2,14 @@
 //
 // Device state of one instance (one image/seed problem, its lambda schedule):
 //   r      int32 [K][n]  residual capacity of the arc p -> p + d_k
-//   e      int32 [n]     excess of p (flow in minus flow out)
-//   rt     int32 [n]     residual capacity of the arc p -> t
+//   e      int32 [n]     net excess of p: flow in minus flow out, minus the
+//                        residual capacity of the arc p -> t
 //   h      int32 [n]     height (distance label); H_INF = "cannot reach t"
 //   inbox  int32 [ntiles][border_words]  flow pushed into a border pixel p
 //                        from p + d_k in another tile, not yet folded into e
 //                        and r: one word per (border pixel, arc leaving the
 //                        tile) pair
-//   rmask  uint16 [n]    bit k: r_k > 0, bit 8: rt > 0, bit 9: e > 0
+//   rmask  uint16 [n]    bit k: r_k > 0, bit 8: e < 0, bit 9: e > 0
 //   masks  uint8 [L][n]  minimal source side for every lambda
 //   hist   int32 [ntiles * TW * TH]  (gap heuristic only) number of pixels
 //                        whose stored label is each value below the size
@@ -67,7 +67,6 @@ struct alignas(16) InstDesc {
     const uint8_t *seed;   // may be null: all free
     int32_t *r;
     int32_t *e;
-    int32_t *rt;
     int32_t *h;
     int32_t *inbox;
     uint16_t *rmask;
@@ -153,10 +152,6 @@ enum PxKind : int { kPxSweep = 0, kPxRelabel, kPxCut, kPxInit, kPxOrient, kPxIni
 int launch_superstep(const StepParams &p, int tile_w, void *stream, void *const *events = nullptr,
                      bool split = false);
 
-// Workgroups of the tile kernel of connectivity K that the current device
-// holds at once (0 if the runtime cannot tell).
-int resident_workgroups(int K, int tile_w);
-
 // Persistent supersteps (one cooperative launch of `grid` workgroups, a
 // multiple of 8 no larger than persist_workgroups(), reading the parameters
 // from a device copy p_dev): up to max_steps
@@ -195,6 +190,9 @@ constexpr size_t engine_bytes(int n) { return engine_clear_bytes(engine_words(n)
 constexpr int kEngineSlots = 4096;    // instances that every handle has room for from the start
 constexpr int kEngineMax = 1 << 16;   // and at most
 constexpr int kEngineTiles = 640;     // tiles of the largest instance it is used for
+// Workgroups of that launch that the current device holds at once (0 if the
+// runtime cannot tell); kset: 4 or 8 when every instance of the work list has
+// that connectivity, 12 for a mixed list.
 int engine_workgroups(int tile_w, int kset);
 int launch_engine(const StepParams &p, const EngineParams &e, int tile_w, int kset, int grid, void *stream);
 

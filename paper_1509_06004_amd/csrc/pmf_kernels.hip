@@ -135,6 +135,9 @@ __device__ __forceinline__ int prefix_count(unsigned long long m) {
 __device__ __forceinline__ void lds_order() { asm volatile("" ::: "memory"); }
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
+// The state bits of a pixel with net excess x (excess minus sink residual).
+__device__ __forceinline__ int x_bits(int x) { return (x < 0 ? kRtBit : 0) | (x > 0 ? kEBit : 0); }
+
 template <int TW, int TH>
 struct Geo {
     static constexpr int NT = kThreads;
@@ -325,8 +328,8 @@ __device__ __forceinline__ void orient_tile(const StepParams &P, const InstDesc 
 //   cs, ct per pixel from (seed, cap_src, cap_snk0, slope, lambda_0), exchanged
 //   when the instance is solved with source and sink swapped (every n-link
 //   then reversed: the residual of p -> q is the capacity of q -> p);
-//   the common part m = min(cs, ct) goes straight from s to t: e = cs - m,
-//   rt = ct - m; r_k = n-link capacity; inbox cleared.
+//   the common part min(cs, ct) goes straight from s to t, which leaves the
+//   net excess e = cs - ct; r_k = n-link capacity; inbox cleared.
 // ---------------------------------------------------------------------------
 template <int K, int TW, int TH, bool COH>
 __device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D, InstState *S, int tl, bool swap,
@@ -377,11 +380,9 @@ __device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D
                 cs = ct;
                 ct = t;
             }
-            const long long m = cs < ct ? cs : ct;
-            const int e = (int)(cs - m);
-            const int rt = (int)(ct - m);
+            const int e = (int)(cs - ct);
             scs += cs;
-            int rm = (rt > 0 ? kRtBit : 0) | (e > 0 ? kEBit : 0);
+            int rm = x_bits(e);
 #pragma unroll
             for (int k = 0; k < K; ++k) {
                 const int qx = gx + DXk(k), qy = gy + DYk(k);
@@ -396,8 +397,7 @@ __device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D
                 if (c > 0) rm |= 1 << k;
             }
             stc<COH>(&gp(D.e)[p], e);
-            stc<COH>(&gp(D.rt)[p], rt);
-            stc<COH>(&gp(D.h)[p], rt > 0 ? 1 : kHInf);
+            stc<COH>(&gp(D.h)[p], e < 0 ? 1 : kHInf);
             stc<COH>(&gp(D.rmask)[p], (uint16_t)rm);
         }
     }
@@ -428,10 +428,12 @@ __device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D
 // kSweep: tile-local push/relabel in LDS.
 //
 // The tile's residuals (one record of K words per cell, so that a pixel reads
-// all of them at once), excess, sink residuals and heights live in LDS with a
-// one-pixel halo.  An active pixel p (e > 0, h < H_INF) pushes d = min(e, r)
-// to the sink when rt > 0 and along admissible arcs (h(p) = h(q) + 1) and, if
-// excess is left and no arc is admissible, is lifted to 1 + min h(q) over its
+// all of them at once), net excess and heights live in LDS with a one-pixel
+// halo.  The net excess is excess minus sink residual: flow that reaches a
+// pixel with a residual sink arc goes to the sink at once, whatever the
+// labels, by the addition alone.  An active pixel p (e > 0, h < H_INF) pushes
+// d = min(e, r) along admissible arcs (h(p) = h(q) + 1) and, if excess is left
+// and no arc is admissible, is lifted to 1 + min h(q) over its
 // residual arcs.  Only the active pixels are processed (a small fraction of
 // the tile once the first steps are done).  All residual and excess updates
 // are LDS atomics: whatever the interleaving of neighbours, every update is
@@ -455,9 +457,8 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     const int W = D.W, H = D.H, n = D.n;
     const int hcap = n + 1;  // no exact distance to t exceeds n
     int32_t *sh_h = lds;             // [HALO] heights
-    int32_t *sh_e = lds + HALO;      // [HALO] excess (tile cells only)
-    int32_t *sh_t = lds + 2 * HALO;  // [HALO] sink residuals (tile cells only)
-    int32_t *sh_r = lds + 3 * HALO;  // [HALO][K] residuals; halo cells: pushes handed over
+    int32_t *sh_e = lds + HALO;      // [HALO] net excess (tile cells only)
+    int32_t *sh_r = lds + 2 * HALO;  // [HALO][K] residuals; halo cells: pushes handed over
     __shared__ int s_nb[9];
     constexpr int kRing = 256;
     __shared__ uint32_t s_dirty[(HALO + 31) / 32];  // a bit per cell whose excess moved in this visit (only it and its neighbours changed)
@@ -472,7 +473,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     // by neighbour tiles), one or two per thread.  Loads of cells outside the
     // image read a clamped in-image address and are replaced by the defaults.
     bool valid[PPT];
-    int e[PPT], rt[PPT], h[PPT], r[PPT][K];
+    int e[PPT], h[PPT], r[PPT][K];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
@@ -481,7 +482,6 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
         e[j] = ldc<COH>(&gp(D.e)[p]);
 #pragma unroll
         for (int k = 0; k < K; ++k) r[j][k] = ldc<COH>(&gp(D.r)[(size_t)k * n + p]);
-        rt[j] = ldc<COH>(&gp(D.rt)[p]);
         h[j] = ldc<COH>(&gp(D.h)[p]);
     }
     // Gap heuristic: no pixel is labelled `gap` (a level that emptied since
@@ -525,7 +525,6 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     for (int j = 0; j < PPT; ++j) {
         const int c = (ly0 + j * RPI + 1) * HW + lx + 1;
         sh_e[c] = valid[j] ? e[j] : 0;
-        sh_t[c] = valid[j] ? rt[j] : 0;
 #pragma unroll
         for (int k = 0; k < K; ++k) sh_r[c * K + k] = valid[j] ? r[j][k] : 0;
         sh_h[c] = valid[j] && h[j] <= gap ? h[j] : kHInf;
@@ -601,12 +600,11 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     };
     // Walking.  Every active pixel (e > 0, h < H_INF) has one token, and a lane
     // that holds a pixel's token is the only one that takes excess out of it,
-    // pushes along its arcs and lifts it.  A step of the lane is: a push to
-    // the sink, then a push along the first admissible arc, or, if there is
-    // none and excess is left, a lift.  The excess leaves the pixel with the
-    // step's last atomic, whose reply tells whether the pixel is still active
-    // (the lane keeps the token); a push into a pixel whose excess was zero
-    // creates that pixel's token.  The lane goes on with the pixel it
+    // pushes along its arcs and lifts it.  A step of the lane is a push along
+    // the first admissible arc or, if there is none, a lift.  The excess
+    // leaves the pixel with the step's last atomic, whose reply tells whether
+    // the pixel is still active (the lane keeps the token); a push that
+    // raises its target's excess above zero creates the target's token.  The lane goes on with the pixel it
     // activated, and queues its own if that stays active, in its wave's
     // ring, from which lanes without a token refill.
     //
@@ -659,13 +657,9 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
                     hq[k] = sh_h[c + DYk(k) * HW + DXk(k)];
                 }
                 const int h = sh_h[c];
-                const int rt = sh_t[c];
                 // other lanes only add to the excess and the residuals
-                int ex = sh_e[c];
+                const int ex = sh_e[c];
                 atomicOr(&s_dirty[c >> 5], 1u << (c & 31));
-                const int dt = imin(ex, rt);
-                ex -= dt;
-                if (dt) sh_t[c] = rt - dt;
                 const int hm1 = h - 1;
                 int rk = 0, to = 0;  // the first admissible arc: its residual; its cell offset and number
 #pragma unroll
@@ -675,16 +669,21 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
                     to = down ? (DYk(k) * HW + DXk(k)) * 8 + k : to;
                 }
                 const int d = imin(ex, rk);
-                int was = 1, nh = h;
+                int nh = h, rest = ex;
+                bool woke = false;  // the push made its target active
                 if (d > 0) {
                     const int k = to & 7;
                     next = c + (to >> 3);
                     atomicSub(&sh_r[c * K + k], d);
                     atomicAdd(&sh_r[next * K + (k ^ 1)], d);
-                    was = atomicAdd(&sh_e[next], d);  // halo cells hold 1: never activated
-                } else if (ex > 0) {
-                    // the sink arc and every admissible arc are saturated:
-                    // lift above the lowest residual neighbour
+                    int was = atomicAdd(&sh_e[next], d);  // halo cells hold 1: never activated
+                    rest = atomicSub(&sh_e[c], d) - d;
+                    // both replies are waited for together
+                    asm volatile("" : "+v"(was));
+                    woke = (was <= 0) & (was + d > 0);
+                } else {
+                    // every admissible arc is saturated: lift above the
+                    // lowest residual neighbour
                     int mn = kHInf;
 #pragma unroll
                     for (int k = 0; k < K; ++k) {
@@ -694,14 +693,9 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
                     nh = mn >= hcap ? kHInf : mn;
                     sh_h[c] = nh;
                 }
-                lds_order();
-                const int out = dt + d;
-                const int rest = atomicSub(&sh_e[c], out) - out;
-                // the reply of the push is waited for together with this one
-                asm volatile("" : "+v"(was));
                 const bool keep = (rest > 0) & (nh < kHInf);
-                again = keep & (was == 0);
-                next = was == 0 ? next : keep ? c : 0;
+                again = keep & woke;
+                next = woke ? next : keep ? c : 0;
             }
             const unsigned long long m = __ballot(again);
             if (m != 0ull) {
@@ -750,8 +744,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
             moved |= s_dirty[q >> 5] >> (q & 31);
         }
         if (!(moved & 1u)) continue;  // as it was
-        const int rt = sh_t[c];
-        int rm = (rt > 0 ? kRtBit : 0) | (e > 0 ? kEBit : 0);
+        int rm = x_bits(e);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int r = sh_r[c * K + k];
@@ -759,7 +752,6 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
             if (r > 0) rm |= 1 << k;
         }
         stc<COH>(&gp(D.e)[p], e);
-        stc<COH>(&gp(D.rt)[p], rt);
         stc<COH>(&gp(D.h)[p], h);
         stc<COH>(&gp(D.rmask)[p], (uint16_t)rm);
     }
@@ -846,7 +838,7 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
     G::ring(min(tid, G::RING - 1), hx, hy);
     const bool hin = x0 + hx - 1 >= 0 && x0 + hx - 1 < W && y0 + hy - 1 >= 0 && y0 + hy - 1 < H;
     const int hq = min(max(y0 + hy - 1, 0), H - 1) * W + min(max(x0 + hx - 1, 0), W - 1);
-    const int hv = first ? (int)ldc<COH>(&gp(D.rmask)[hq]) : ldc<COH>(&gp(D.h)[hq]);
+    const int hv = first ? kHInf : ldc<COH>(&gp(D.h)[hq]);
     // the tile's active count under the previous labels, read now so that
     // the end of the visit does not wait for it
     const int cnt_prev = (!first && tid == 0) ? ldc<COH>(&gp(D.tile_cnt)[tl]) : 0;
@@ -888,8 +880,8 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
             const int ein = sh_in[c];
             if (ein && valid[j]) {
                 const int p = (y0 + ly0 + j * RPI) * W + x0 + lx;
-                g_add(&gp(D.e)[p], ein);
-                rm[j] |= (uint32_t)sh_ib[c] | kEBit;
+                const int x = __hip_atomic_fetch_add(&gp(D.e)[p], ein, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + ein;
+                rm[j] = (rm[j] & ~(uint32_t)(kRtBit | kEBit)) | (uint32_t)(sh_ib[c] | x_bits(x));
                 stc<COH>(&gp(D.rmask)[p], (uint16_t)rm[j]);
             }
         }
@@ -903,14 +895,16 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
         sh_rm[(ly0 + j * RPI + 1) * HW + lx + 1] = (int32_t)rm[j];
     }
     if (tid < G::RING)
-        sh_d[hy * HW + hx] = !hin ? kHInf : first ? ((hv & kRtBit) ? 1 : kHInf) : hv;
+        sh_d[hy * HW + hx] = hin ? hv : kHInf;
     __syncthreads();
     // After the first pass of a relabel every stored label is an upper bound
     // of the true distance that only decreases, so the tile may publish its
     // improved labels and take newer halo labels written by neighbour tiles
     // during this same launch, several times per visit (exchange rounds).
-    // Stale reads only delay convergence.  The first pass keeps one round: its
-    // neighbours' stored labels are still those of the previous phase.
+    // Stale reads only delay convergence.  The first pass keeps one round and
+    // takes no halo labels: its neighbours' stored labels are still those of
+    // the previous phase, and their sink residuals may be about to shrink by
+    // the inflow they fold in this same pass.
     int dpub[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) dpub[j] = d0[j];
@@ -1075,7 +1069,7 @@ __device__ __forceinline__ void cut_tile_swapped(const StepParams &P, const Inst
     const int W = D.W, H = D.H, n = D.n;
     GLOBAL uint8_t *mask = gp(D.masks) + (size_t)kk * n;
     const int dlam = kk + 1 < D.L ? gp(D.lambdas)[kk + 1] - gp(D.lambdas)[kk] : 0;
-    int hv[PPT], rmv[PPT], ev[PPT], rtv[PPT], sdv[PPT], slv[PPT];
+    int hv[PPT], rmv[PPT], ev[PPT], sdv[PPT], slv[PPT];
     bool valid[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
@@ -1085,7 +1079,6 @@ __device__ __forceinline__ void cut_tile_swapped(const StepParams &P, const Inst
         hv[j] = ldc<COH>(&gp(D.h)[p]);
         rmv[j] = ldc<COH>(&gp(D.rmask)[p]);
         ev[j] = ldc<COH>(&gp(D.e)[p]);
-        rtv[j] = ldc<COH>(&gp(D.rt)[p]);
         sdv[j] = 0;
         slv[j] = 1;
         if (dlam > 0) {
@@ -1100,16 +1093,14 @@ __device__ __forceinline__ void cut_tile_swapped(const StepParams &P, const Inst
         if (!valid[j]) continue;
         const int p = (y0 + ly0 + j * RPI) * W + x0 + lx;
         mask[p] = hv[j] < kHInf ? 1 : 0;  // not read again by this launch
-        if (rmv[j] & kEBit) se += ev[j];
+        if (ev[j] > 0) se += ev[j];
         const int sl = sdv[j] == 0 ? slv[j] : 0;
         if (dlam > 0 && sl > 0) {
             const int inc = (int)((long long)sl * dlam);  // <= INF: checked at init
             sraise += inc;
-            const int d = inc < rtv[j] ? inc : rtv[j];
-            const int nrt = rtv[j] - d, ne = ev[j] + (inc - d);
-            stc<COH>(&gp(D.rt)[p], nrt);
+            const int ne = ev[j] + inc;
             stc<COH>(&gp(D.e)[p], ne);
-            const int rm = (rmv[j] & ~(kRtBit | kEBit)) | (nrt > 0 ? kRtBit : 0) | (ne > 0 ? kEBit : 0);
+            const int rm = (rmv[j] & ~(kRtBit | kEBit)) | x_bits(ne);
             if (rm != rmv[j]) stc<COH>(&gp(D.rmask)[p], (uint16_t)rm);
             act |= ne > 0 && hv[j] < kHInf;
         }
@@ -1154,7 +1145,7 @@ __device__ __forceinline__ void cut_tile(const StepParams &P, const InstDesc &D,
     const int dlam = raise ? gp(D.lambdas)[kk + 1] - gp(D.lambdas)[kk] : 0;
     // Every global load is issued before any is used (cells outside the image
     // read a clamped in-image address and take the defaults).
-    int m[PPT], m0[PPT], rmv[PPT], ev[PPT], rtv[PPT], sdv[PPT], slv[PPT];
+    int m[PPT], m0[PPT], rmv[PPT], ev[PPT], sdv[PPT], slv[PPT];
     bool valid[PPT];
     long long se = 0;
 #pragma unroll
@@ -1164,12 +1155,11 @@ __device__ __forceinline__ void cut_tile(const StepParams &P, const InstDesc &D,
         const int p = min(gy, H - 1) * W + min(gx, W - 1);
         rmv[j] = ldc<COH>(&gp(D.rmask)[p]);
         m[j] = 0;
-        ev[j] = rtv[j] = sdv[j] = 0;
+        ev[j] = sdv[j] = 0;
         slv[j] = 1;
         if (first) {
             ev[j] = ldc<COH>(&gp(D.e)[p]);
             if (dlam > 0) {
-                rtv[j] = ldc<COH>(&gp(D.rt)[p]);
                 if (D.seed) sdv[j] = gp(D.seed)[p];
                 if (D.slope) slv[j] = gp(D.slope)[p];
             }
@@ -1191,13 +1181,16 @@ __device__ __forceinline__ void cut_tile(const StepParams &P, const InstDesc &D,
         } else if (first) {
             m[j] = (rmv[j] & kEBit) ? 1 : 0;
             if (m[j]) se += ev[j];
-            // raise the sink residuals to the next lambda (warm start)
+            // raise the sink capacities to the next lambda (warm start); a
+            // neighbour tile that finds the excess bit already cleared takes
+            // the pixel from the mask in its next pass
             const int sl = sdv[j] == 0 ? slv[j] : 0;
             if (dlam > 0 && sl > 0) {
                 const int p = (y0 + ly0 + j * RPI) * W + x0 + lx;
-                const int nrt = rtv[j] + sl * dlam;
-                stc<COH>(&gp(D.rt)[p], nrt);
-                if (nrt > 0 && !(rmv[j] & kRtBit)) stc<COH>(&gp(D.rmask)[p], (uint16_t)(rmv[j] | kRtBit));
+                const int ne = ev[j] - sl * dlam;
+                stc<COH>(&gp(D.e)[p], ne);
+                const int rm = (rmv[j] & ~(kRtBit | kEBit)) | x_bits(ne);
+                if (rm != rmv[j]) stc<COH>(&gp(D.rmask)[p], (uint16_t)rm);
             }
         }
         m0[j] = m[j];
@@ -1574,7 +1567,7 @@ __device__ void tile_work(const StepParams &P, int ws, int wp, int32_t *lds, int
 // LDS also allows (four workgroups per CU).
 template <int K, int TW, int TH, bool GAP, bool TIMED = false>
 __global__ __launch_bounds__(kThreads, K == 4 ? 4 : 1) void k_step(StepParams P, int ws, int wp) {
-    __shared__ int32_t lds[(3 + K) * (TW + 2) * (TH + 2)];  // sweep layout; passes use 4 planes
+    __shared__ int32_t lds[(2 + K) * (TW + 2) * (TH + 2)];  // sweep layout; passes use 4 planes
     __shared__ int s_red[32];  // [0]: block_count_ballot, [8..15]: block_vote, [16..31]: block_any
     __shared__ unsigned long long s_sum;
     tile_work<K, TW, TH, GAP>(P, ws, wp, lds, s_red, &s_sum);
@@ -2079,7 +2072,7 @@ __global__ __launch_bounds__(kThreads) void k_engine_start(StepParams P, EngineP
 template <int KSET, int TW, int TH>
 __global__ __launch_bounds__(kThreads, KSET == 4 ? 4 : 3) void k_engine(StepParams P, EngineParams E) {
     constexpr int KM = KSET == 4 ? 4 : 8;
-    __shared__ int32_t lds[(3 + KM) * (TW + 2) * (TH + 2)];  // sweep layout; passes use 4 planes
+    __shared__ int32_t lds[(2 + KM) * (TW + 2) * (TH + 2)];  // sweep layout; passes use 4 planes
     __shared__ int s_red[32];  // [0]: block_count_ballot, [8..15]: block_vote, [16..31]: block_any
     __shared__ unsigned long long s_sum;
     __shared__ EngTask s_task;
@@ -2276,26 +2269,11 @@ static int launch_tw(const StepParams &p, hipStream_t s, void *const *ev, bool s
     return n;
 }
 
-int resident_workgroups(int K, int tile_w) {
-    int dev = 0, cus = 0, per = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        return 0;
-    hipError_t e;
-    if (tile_w == 64)
-        e = K == 8 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_step<8, 64, 16, false>, kThreads, 0)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_step<4, 64, 16, false>, kThreads, 0);
-    else
-        e = K == 8 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_step<8, 32, 32, false>, kThreads, 0)
-                   : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_step<4, 32, 32, false>, kThreads, 0);
-    return e == hipSuccess ? per * cus : 0;
-}
-
 // Dynamic LDS of a persistent launch: the sweep layout of its connectivity
 // (the 8-connected one for mixed lists).
 static unsigned persist_lds_bytes(int tile_w, int kset) {
     const int tw = tile_w == 64 ? 64 : 32, th = 1024 / tw, K = kset == 4 ? 4 : 8;
-    return (unsigned)((3 + K) * (tw + 2) * (th + 2) * 4);
+    return (unsigned)((2 + K) * (tw + 2) * (th + 2) * 4);
 }
 
 template <int TW, int TH>
