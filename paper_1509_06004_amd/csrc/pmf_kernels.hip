@@ -431,10 +431,10 @@ __device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D
 // all of them at once), net excess and heights live in LDS with a one-pixel
 // halo.  The net excess is excess minus sink residual: flow that reaches a
 // pixel with a residual sink arc goes to the sink at once, whatever the
-// labels, by the addition alone.  An active pixel p (e > 0, h < H_INF) pushes
-// d = min(e, r) along admissible arcs (h(p) = h(q) + 1) and, if excess is left
-// and no arc is admissible, is lifted to 1 + min h(q) over its
-// residual arcs.  Only the active pixels are processed (a small fraction of
+// labels, by the addition alone.  An active pixel p (e > 0, h < H_INF) takes
+// the label 1 + min h(q) over its residual arcs and pushes d = min(e, r) along
+// the arc of that minimum (so it is lifted exactly when no arc was admissible,
+// h(p) = h(q) + 1).  Only the active pixels are processed (a small fraction of
 // the tile once the first steps are done).  All residual and excess updates
 // are LDS atomics: whatever the interleaving of neighbours, every update is
 // applied exactly once, a pixel never sends more than the excess and residual
@@ -600,21 +600,26 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     };
     // Walking.  Every active pixel (e > 0, h < H_INF) has one token, and a lane
     // that holds a pixel's token is the only one that takes excess out of it,
-    // pushes along its arcs and lifts it.  A step of the lane is a push along
-    // the first admissible arc or, if there is none, a lift.  The excess
-    // leaves the pixel with the step's last atomic, whose reply tells whether
-    // the pixel is still active (the lane keeps the token); a push that
-    // raises its target's excess above zero creates the target's token.  The lane goes on with the pixel it
-    // activated, and queues its own if that stays active, in its wave's
-    // ring, from which lanes without a token refill.
+    // pushes along its arcs and sets its label.  A step of the lane is a push
+    // to the lowest residual neighbour, the pixel's label set one above it.
+    // The excess leaves the pixel with the step's last atomic, whose reply
+    // tells whether the pixel is still active (the lane keeps the token); a
+    // push that raises its target's excess above zero creates the target's
+    // token.  The lane goes on with the pixel it activated, and queues its
+    // own if that stays active, in its wave's ring, from which lanes without
+    // a token refill.
     //
     // Why: a sweep is bound by the latency of its steps (a wave works on some
     // 15 pixels at a time, few of its lanes).  A step is two LDS round trips
-    // and some 60 instructions, 0.43 us; listing the tile's active pixels by
+    // and some 90 instructions, 0.4 us; listing the tile's active pixels by
     // ballots before each step, with a workgroup vote to end, was 1.1 us.
-    // All admissible arcs in one step made it 0.56 us at 4 arcs and 0.95 at
-    // 8, for few steps less.  Waves need no barrier: one without tokens is
-    // done, since nobody hands it any.  A token that finds the ring full is
+    // Pushing along every admissible arc in one step made it 0.56 us at 4
+    // arcs and 0.95 at 8, for few steps less.  Lifting in a step of its own
+    // (a third of the steps) made 25 seeds x 20 lambdas of 500 x 375 24.2
+    // instead of 22.5 ms; reading the target's record along with the push's
+    // replies, one round trip instead of two, 24.6: the selects it needs cost
+    // more than the wait.  Waves need no barrier: one without tokens is done,
+    // since nobody hands it any.  A token that finds the ring full is
     // dropped: its pixel waits for the next visit.
     constexpr int RC = kRing;  // ring entries per wave
     uint16_t *ring = s_slot + (tid >> 6) * RC;
@@ -656,46 +661,36 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
                     r[k] = sh_r[c * K + k];
                     hq[k] = sh_h[c + DYk(k) * HW + DXk(k)];
                 }
-                const int h = sh_h[c];
                 // other lanes only add to the excess and the residuals
                 const int ex = sh_e[c];
                 atomicOr(&s_dirty[c >> 5], 1u << (c & 31));
-                const int hm1 = h - 1;
-                int rk = 0, to = 0;  // the first admissible arc: its residual; its cell offset and number
+                // the lowest residual neighbour: its label, residual, cell
+                // offset and arc number
+                int mn = kHInf, rk = 0, to = 0;
 #pragma unroll
-                for (int k = K - 1; k >= 0; --k) {
-                    const bool down = (hq[k] == hm1) & (r[k] > 0);
-                    rk = down ? r[k] : rk;
-                    to = down ? (DYk(k) * HW + DXk(k)) * 8 + k : to;
+                for (int k = 0; k < K; ++k) {
+                    const int cand = r[k] > 0 ? hq[k] : kHInf;
+                    const bool low = cand < mn;
+                    mn = low ? cand : mn;
+                    rk = low ? r[k] : rk;
+                    to = low ? (DYk(k) * HW + DXk(k)) * 8 + k : to;
                 }
-                const int d = imin(ex, rk);
-                int nh = h, rest = ex;
-                bool woke = false;  // the push made its target active
-                if (d > 0) {
-                    const int k = to & 7;
+                const bool dead = mn + 1 >= hcap;
+                sh_h[c] = dead ? kHInf : mn + 1;
+                if (!dead) {
+                    const int k = to & 7, d = imin(ex, rk);
                     next = c + (to >> 3);
                     atomicSub(&sh_r[c * K + k], d);
                     atomicAdd(&sh_r[next * K + (k ^ 1)], d);
                     int was = atomicAdd(&sh_e[next], d);  // halo cells hold 1: never activated
-                    rest = atomicSub(&sh_e[c], d) - d;
+                    lds_order();
+                    const bool keep = atomicSub(&sh_e[c], d) > d;
                     // both replies are waited for together
                     asm volatile("" : "+v"(was));
-                    woke = (was <= 0) & (was + d > 0);
-                } else {
-                    // every admissible arc is saturated: lift above the
-                    // lowest residual neighbour
-                    int mn = kHInf;
-#pragma unroll
-                    for (int k = 0; k < K; ++k) {
-                        const int cand = r[k] > 0 ? hq[k] + 1 : kHInf;
-                        mn = cand < mn ? cand : mn;
-                    }
-                    nh = mn >= hcap ? kHInf : mn;
-                    sh_h[c] = nh;
+                    const bool woke = (was <= 0) & (was + d > 0);
+                    again = keep & woke;
+                    next = woke ? next : keep ? c : 0;
                 }
-                const bool keep = (rest > 0) & (nh < kHInf);
-                again = keep & woke;
-                next = woke ? next : keep ? c : 0;
             }
             const unsigned long long m = __ballot(again);
             if (m != 0ull) {
