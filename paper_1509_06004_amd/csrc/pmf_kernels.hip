@@ -461,11 +461,12 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     int32_t *sh_r = lds + 2 * HALO;  // [HALO][K] residuals; halo cells: pushes handed over
     __shared__ int s_nb[9];
     constexpr int kRing = 256;
-    __shared__ uint32_t s_dirty[(HALO + 31) / 32];  // a bit per cell whose excess moved in this visit (only it and its neighbours changed)
+    // cells whose excess moved in this visit: only they and their neighbours changed
+    __shared__ uint8_t s_moved[(HALO + 3) / 4 * 4];
     __shared__ uint16_t s_slot[kThreads / 64 * kRing];  // per wave: cells of active pixels waiting for a lane
 
     if (tid < 9) s_nb[tid] = 0;
-    if (tid < (HALO + 31) / 32) s_dirty[tid] = 0u;
+    for (int i = tid; i < (HALO + 3) / 4; i += kThreads) reinterpret_cast<uint32_t *>(s_moved)[i] = 0u;
     if (tid == 0) g_and(&gp(D.tile_act)[tl], ~2u);  // about to drain the inbox
     // Every global load of the visit is issued before any is used: the halo
     // cell heights of the neighbour tiles (one ring cell per thread), the
@@ -538,7 +539,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
             const int c = (by + 1) * HW + bx + 1;
             atomicAdd(&sh_e[c], ibv[q]);
             atomicAdd(&sh_r[c * K + k], ibv[q]);
-            atomicOr(&s_dirty[c >> 5], 1u << (c & 31));
+            s_moved[c] = 1;
         }
     }
     __syncthreads();
@@ -593,7 +594,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
                 const int c = (by + 1) * HW + bx + 1;
                 atomicAdd(&sh_e[c], v);
                 atomicAdd(&sh_r[c * K + k], v);
-                atomicOr(&s_dirty[c >> 5], 1u << (c & 31));
+                s_moved[c] = 1;
             }
         }
         __syncthreads();
@@ -663,7 +664,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
                 }
                 // other lanes only add to the excess and the residuals
                 const int ex = sh_e[c];
-                atomicOr(&s_dirty[c >> 5], 1u << (c & 31));
+                s_moved[c] = 1;
                 // the lowest residual neighbour: its label, residual, cell
                 // offset and arc number
                 int mn = kHInf, rk = 0, to = 0;
@@ -732,13 +733,10 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
                 if (h < D.hsize) g_add(&gp(D.hist)[h], 1);
             }
         }
-        uint32_t moved = s_dirty[c >> 5] >> (c & 31);
+        int moved = s_moved[c];
 #pragma unroll
-        for (int k = 0; k < K; ++k) {
-            const int q = c + DYk(k) * HW + DXk(k);
-            moved |= s_dirty[q >> 5] >> (q & 31);
-        }
-        if (!(moved & 1u)) continue;  // as it was
+        for (int k = 0; k < K; ++k) moved |= s_moved[c + DYk(k) * HW + DXk(k)];
+        if (!moved) continue;  // as it was
         int rm = x_bits(e);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
