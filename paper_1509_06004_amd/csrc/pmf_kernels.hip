@@ -901,7 +901,14 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
     int dpub[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) dpub[j] = d0[j];
-    const int rounds = first ? 1 : xrounds;
+    int rounds = first ? 1 : xrounds;
+    if (first) {
+        // without a pixel that has sink residual nothing is labelled yet
+        int seeds = 0;
+#pragma unroll
+        for (int j = 0; j < PPT; ++j) seeds |= d[j] < kHInf;
+        if (!block_any(seeds != 0, s_red + 24)) rounds = 0;
+    }
     for (int round = 0; round < rounds; ++round) {
     // Relaxation rounds; the convergence check (a barrier) runs every 4
     // rounds.  Labels only decrease and every value read is an upper bound of
@@ -1002,7 +1009,10 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
     }
     if (!block_any(got != 0, s_red + 24)) break;
     }
-    int changed = first ? 1 : 0;
+    // The first pass took every halo label for H_INF, so a tile's neighbours
+    // have something new to read when it holds a label at all (and the tile
+    // itself when its relaxation was cut short, which needs a label too).
+    int changed = 0;
     bool act[PPT], one[PPT];
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
@@ -1011,7 +1021,7 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
         act[j] = (rm[j] & kEBit) && d[j] < kHInf;  // rm = 0 outside the image
         one[j] = first && d[j] == 1;
         if (gx >= W || gy >= H) continue;
-        if (first || d[j] != d0[j]) changed = 1;
+        if (first ? d[j] < kHInf : d[j] != d0[j]) changed = 1;
         if (first || d[j] != dpub[j]) stc<COH>(&gp(D.h)[gy * W + gx], d[j]);
         // gap heuristic: the label histogram follows every change after the
         // first pass (which sets every label to 1 or H_INF and clears it)
