@@ -69,26 +69,37 @@ int check_instance(const pmf_instance &I) {
 // Byte offsets of one instance's planes inside its block.
 struct BlockLayout {
     size_t r, e, h, inbox, rmask, masks, tile_act, tile_chg, tile_cnt, hist, total;
-    int tiles_x, tiles_y;
+    int tiles_x, tiles_y, pitch;
 };
 
+// A block has room for K + 3 unpadded int32 planes, of which the state needs
+// K + 2.  The rest goes into rows of whole 128-byte lines (a multiple of 32
+// pixels), where it is enough for that (from some 150 pixels of width on): a
+// tile's rows then are whole lines.  A visit of a 500-pixel-wide image reads
+// and writes half the lines (loads 10.1 -> 5.0 us, stores 6.1 -> 2.9 us with
+// every workgroup of the device at it).
 BlockLayout block_layout(const pmf_instance &I, int tw, int th, bool gap) {
     BlockLayout b;
     b.tiles_x = (I.W + tw - 1) / tw;
     b.tiles_y = (I.H + th - 1) / th;
     const size_t px = (size_t)I.W * I.H, K = (size_t)I.K, nt = (size_t)b.tiles_x * b.tiles_y;
+    const size_t planes = align_up(4 * K * px) + 3 * align_up(4 * px) + align_up(2 * px);
+    b.pitch = (I.W + 31) / 32 * 32;
+    const size_t pp = (size_t)b.pitch * I.H;
+    if (align_up(4 * K * pp) + 2 * align_up(4 * pp) + align_up(2 * pp) > planes) b.pitch = I.W;
+    const size_t sp = (size_t)b.pitch * I.H;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         size_t at = off;
         off = align_up(off + bytes);
         return at;
     };
-    b.r = take(4 * K * px);
-    b.e = take(4 * px);
-    take(4 * px);
-    b.h = take(4 * px);
+    b.r = take(4 * K * sp);
+    b.e = take(4 * sp);
+    b.h = take(4 * sp);
+    b.rmask = take(2 * sp);
+    off = planes;
     b.inbox = take(4 * nt * (size_t)border_words(I.K, tw, th));
-    b.rmask = take(2 * px);
     b.masks = take((size_t)I.L * px);
     b.tile_act = take(4 * nt);
     b.tile_chg = take(2 * nt);
@@ -500,6 +511,7 @@ int submit(pmf_handle *h, const pmf_instance *inst, int n, int64_t *flows_out, i
         D.slot_id = id;
         D.check_prev = check_prev ? check_prev[i] : 0;
         D.tile_w = h->tw;
+        D.pitch = B.pitch;
         D.lambdas = I.lambdas;
         D.nlink = I.nlink;
         D.cap_src = I.cap_src;

@@ -13,7 +13,9 @@
 //   masks  uint8 [L][n]  minimal source side for every lambda
 //   hist   int32 [ntiles * TW * TH]  (gap heuristic only) number of pixels
 //                        whose stored label is each value below the size
-// All pixel planes are row-major with pitch W, 256-byte aligned.
+// All pixel planes are row-major, 256-byte aligned; r, e, h and rmask have
+// InstDesc::pitch pixels from row to row (their planes pitch * H entries
+// where n is written above), masks W.
 #pragma once
 
 #include <stdint.h>
@@ -78,7 +80,7 @@ struct alignas(16) InstDesc {
     int32_t *tile_cnt;   // [ntiles] active pixels under the current labels
     int32_t *hist;       // gap heuristic: pixels per label value (null when off)
     int32_t hsize;       // entries of hist (ntiles * TW * TH); larger labels are not counted
-    int32_t pad2;
+    int32_t pitch;       // pixels from row to row of r, e, h and rmask (>= W)
 };
 
 struct alignas(16) InstState {

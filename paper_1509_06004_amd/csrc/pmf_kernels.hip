@@ -338,7 +338,8 @@ __device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D
     const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
-    const int W = D.W, H = D.H, n = D.n;
+    const int W = D.W, H = D.H, n = D.n, WP = D.pitch;
+    const size_t np = (size_t)WP * H;
     const long long lam0 = gp(D.lambdas)[0];
     const long long lamL = gp(D.lambdas)[D.L - 1];
     const int32_t nlmax = ((1 << 30) - 1) / K;
@@ -372,7 +373,7 @@ __device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D
             const int ly = ly0 + j * G::RPI;
             const int gx = x0 + lx, gy = y0 + ly;
             if (gx >= W || gy >= H) continue;
-            const int p = gy * W + gx;
+            const int p = gy * WP + gx;
             long long cs, ct;
             terminal_caps(tin[jj], lam0, lamL, cs, ct, err);
             if (swap) {
@@ -393,7 +394,7 @@ __device__ __forceinline__ void init_tile(const StepParams &P, const InstDesc &D
                 if (swap) c = on ? rv[jj][k] : 0;
                 if (!on || c < 0) c = 0;
                 if (c > nlmax) c = nlmax;
-                stc<COH>(&gp(D.r)[(size_t)k * n + p], c);
+                stc<COH>(&gp(D.r)[(size_t)k * np + p], c);
                 if (c > 0) rm |= 1 << k;
             }
             stc<COH>(&gp(D.e)[p], e);
@@ -454,7 +455,8 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
-    const int W = D.W, H = D.H, n = D.n;
+    const int W = D.W, H = D.H, n = D.n, WP = D.pitch;
+    const size_t np = (size_t)WP * H;
     const int hcap = n + 1;  // no exact distance to t exceeds n
     int32_t *sh_h = lds;             // [HALO] heights
     int32_t *sh_e = lds + HALO;      // [HALO] net excess (tile cells only)
@@ -479,10 +481,10 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     for (int j = 0; j < PPT; ++j) {
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
         valid[j] = gx < W && gy < H;
-        const int p = min(gy, H - 1) * W + min(gx, W - 1);
+        const int p = min(gy, H - 1) * WP + min(gx, W - 1);
         e[j] = ldc<COH>(&gp(D.e)[p]);
 #pragma unroll
-        for (int k = 0; k < K; ++k) r[j][k] = ldc<COH>(&gp(D.r)[(size_t)k * n + p]);
+        for (int k = 0; k < K; ++k) r[j][k] = ldc<COH>(&gp(D.r)[(size_t)k * np + p]);
         h[j] = ldc<COH>(&gp(D.h)[p]);
     }
     // Gap heuristic: no pixel is labelled `gap` (a level that emptied since
@@ -499,7 +501,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     G::ring(min(tid, G::RING - 1), hx, hy);
     const int hc = hy * HW + hx;
     const bool hin = x0 + hx - 1 >= 0 && x0 + hx - 1 < W && y0 + hy - 1 >= 0 && y0 + hy - 1 < H;
-    const int hv = ldc<COH>(&gp(D.h)[min(max(y0 + hy - 1, 0), H - 1) * W + min(max(x0 + hx - 1, 0), W - 1)]);
+    const int hv = ldc<COH>(&gp(D.h)[min(max(y0 + hy - 1, 0), H - 1) * WP + min(max(x0 + hx - 1, 0), W - 1)]);
     using B = Border<K, TW, TH>;
     constexpr int NBP = (B::E + kThreads - 1) / kThreads;  // inbox words per thread
     GLOBAL int32_t *const inbox = gp(D.inbox) + (size_t)tl * B::E;
@@ -714,7 +716,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
         killed[j] = false;
         if (!valid[j]) continue;
         const int ly = ly0 + j * RPI;
-        const int p = (y0 + ly) * W + x0 + lx;
+        const int p = (y0 + ly) * WP + x0 + lx;
         const int c = (ly + 1) * HW + lx + 1;
         const int h0 = h[j];
         const int e = sh_e[c];
@@ -741,7 +743,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const int r = sh_r[c * K + k];
-            stc<COH>(&gp(D.r)[(size_t)k * n + p], r);
+            stc<COH>(&gp(D.r)[(size_t)k * np + p], r);
             if (r > 0) rm |= 1 << k;
         }
         stc<COH>(&gp(D.e)[p], e);
@@ -805,7 +807,8 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
     const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
-    const int W = D.W, H = D.H, n = D.n;
+    const int W = D.W, H = D.H, WP = D.pitch;
+    const size_t np = (size_t)WP * H;
     const bool first = sub == 0;
     const int cur = sub & 1;  // tile_chg parity written by this pass
     int32_t *sh_d = lds;              // [HALO] labels
@@ -823,14 +826,14 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
     for (int j = 0; j < PPT; ++j) {
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
         valid[j] = gx < W && gy < H;
-        const int p = min(gy, H - 1) * W + min(gx, W - 1);
+        const int p = min(gy, H - 1) * WP + min(gx, W - 1);
         rm[j] = ldc<COH>(&gp(D.rmask)[p]);
         d[j] = first ? 0 : ldc<COH>(&gp(D.h)[p]);
     }
     int hx, hy;
     G::ring(min(tid, G::RING - 1), hx, hy);
     const bool hin = x0 + hx - 1 >= 0 && x0 + hx - 1 < W && y0 + hy - 1 >= 0 && y0 + hy - 1 < H;
-    const int hq = min(max(y0 + hy - 1, 0), H - 1) * W + min(max(x0 + hx - 1, 0), W - 1);
+    const int hq = min(max(y0 + hy - 1, 0), H - 1) * WP + min(max(x0 + hx - 1, 0), W - 1);
     const int hv = first ? kHInf : ldc<COH>(&gp(D.h)[hq]);
     // the tile's active count under the previous labels, read now so that
     // the end of the visit does not wait for it
@@ -861,7 +864,7 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
                 B::pair(i, bx, by, k);
                 const int c = (by + 1) * HW + bx + 1;
                 stc<COH>(&inbox[i], 0);
-                g_add(&gp(D.r)[(size_t)k * n + (y0 + by) * W + x0 + bx], v);
+                g_add(&gp(D.r)[(size_t)k * np + (y0 + by) * WP + x0 + bx], v);
                 atomicAdd(&sh_in[c], v);
                 atomicOr(&sh_ib[c], 1 << k);
             }
@@ -872,7 +875,7 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
             const int c = (ly0 + j * RPI + 1) * HW + lx + 1;
             const int ein = sh_in[c];
             if (ein && valid[j]) {
-                const int p = (y0 + ly0 + j * RPI) * W + x0 + lx;
+                const int p = (y0 + ly0 + j * RPI) * WP + x0 + lx;
                 const int x = __hip_atomic_fetch_add(&gp(D.e)[p], ein, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + ein;
                 rm[j] = (rm[j] & ~(uint32_t)(kRtBit | kEBit)) | (uint32_t)(sh_ib[c] | x_bits(x));
                 stc<COH>(&gp(D.rmask)[p], (uint16_t)rm[j]);
@@ -991,7 +994,7 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
         const int ly = ly0 + j * RPI;
         const int gx = x0 + lx, gy = y0 + ly;
         if (gx < W && gy < H && d[j] < dpub[j]) {
-            st_agent(&gp(D.h)[gy * W + gx], d[j]);
+            st_agent(&gp(D.h)[gy * WP + gx], d[j]);
             dpub[j] = d[j];
         }
     }
@@ -1001,7 +1004,7 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
         G::ring(i, hx, hy);
         const int gx = x0 + hx - 1, gy = y0 + hy - 1;
         if (gx < 0 || gx >= W || gy < 0 || gy >= H) continue;
-        const int v = ld_agent(&gp(D.h)[gy * W + gx]);
+        const int v = ld_agent(&gp(D.h)[gy * WP + gx]);
         if (v < sh_d[hy * HW + hx]) {
             sh_d[hy * HW + hx] = v;
             got = 1;
@@ -1022,7 +1025,7 @@ __device__ __forceinline__ void relabel_tile(const StepParams &P, const InstDesc
         one[j] = first && d[j] == 1;
         if (gx >= W || gy >= H) continue;
         if (first ? d[j] < kHInf : d[j] != d0[j]) changed = 1;
-        if (first || d[j] != dpub[j]) stc<COH>(&gp(D.h)[gy * W + gx], d[j]);
+        if (first || d[j] != dpub[j]) stc<COH>(&gp(D.h)[gy * WP + gx], d[j]);
         // gap heuristic: the label histogram follows every change after the
         // first pass (which sets every label to 1 or H_INF and clears it)
         if (GAP && !first && d[j] != d0[j]) {
@@ -1069,7 +1072,7 @@ __device__ __forceinline__ void cut_tile_swapped(const StepParams &P, const Inst
     const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
-    const int W = D.W, H = D.H, n = D.n;
+    const int W = D.W, H = D.H, n = D.n, WP = D.pitch;
     GLOBAL uint8_t *mask = gp(D.masks) + (size_t)kk * n;
     const int dlam = kk + 1 < D.L ? gp(D.lambdas)[kk + 1] - gp(D.lambdas)[kk] : 0;
     int hv[PPT], rmv[PPT], ev[PPT], sdv[PPT], slv[PPT];
@@ -1079,9 +1082,10 @@ __device__ __forceinline__ void cut_tile_swapped(const StepParams &P, const Inst
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
         valid[j] = gx < W && gy < H;
         const int p = min(gy, H - 1) * W + min(gx, W - 1);
-        hv[j] = ldc<COH>(&gp(D.h)[p]);
-        rmv[j] = ldc<COH>(&gp(D.rmask)[p]);
-        ev[j] = ldc<COH>(&gp(D.e)[p]);
+        const int ps = min(gy, H - 1) * WP + min(gx, W - 1);
+        hv[j] = ldc<COH>(&gp(D.h)[ps]);
+        rmv[j] = ldc<COH>(&gp(D.rmask)[ps]);
+        ev[j] = ldc<COH>(&gp(D.e)[ps]);
         sdv[j] = 0;
         slv[j] = 1;
         if (dlam > 0) {
@@ -1102,9 +1106,10 @@ __device__ __forceinline__ void cut_tile_swapped(const StepParams &P, const Inst
             const int inc = (int)((long long)sl * dlam);  // <= INF: checked at init
             sraise += inc;
             const int ne = ev[j] + inc;
-            stc<COH>(&gp(D.e)[p], ne);
+            const int ps = (y0 + ly0 + j * RPI) * WP + x0 + lx;
+            stc<COH>(&gp(D.e)[ps], ne);
             const int rm = (rmv[j] & ~(kRtBit | kEBit)) | x_bits(ne);
-            if (rm != rmv[j]) stc<COH>(&gp(D.rmask)[p], (uint16_t)rm);
+            if (rm != rmv[j]) stc<COH>(&gp(D.rmask)[ps], (uint16_t)rm);
             act |= ne > 0 && hv[j] < kHInf;
         }
     }
@@ -1137,7 +1142,7 @@ __device__ __forceinline__ void cut_tile(const StepParams &P, const InstDesc &D,
     const int tid = thread_id(), lx = tid % TW, ly0 = tid / TW;
     const int tx = tl % D.tiles_x, ty = tl / D.tiles_x;
     const int x0 = tx * TW, y0 = ty * TH;
-    const int W = D.W, H = D.H, n = D.n;
+    const int W = D.W, H = D.H, n = D.n, WP = D.pitch;
     const bool first = sub == 0;
     const int cur = sub & 1;  // tile_chg parity written by this pass
     GLOBAL uint8_t *mask = gp(D.masks) + (size_t)kk * n;
@@ -1156,12 +1161,13 @@ __device__ __forceinline__ void cut_tile(const StepParams &P, const InstDesc &D,
         const int gx = x0 + lx, gy = y0 + ly0 + j * RPI;
         valid[j] = gx < W && gy < H;
         const int p = min(gy, H - 1) * W + min(gx, W - 1);
-        rmv[j] = ldc<COH>(&gp(D.rmask)[p]);
+        const int ps = min(gy, H - 1) * WP + min(gx, W - 1);
+        rmv[j] = ldc<COH>(&gp(D.rmask)[ps]);
         m[j] = 0;
         ev[j] = sdv[j] = 0;
         slv[j] = 1;
         if (first) {
-            ev[j] = ldc<COH>(&gp(D.e)[p]);
+            ev[j] = ldc<COH>(&gp(D.e)[ps]);
             if (dlam > 0) {
                 if (D.seed) sdv[j] = gp(D.seed)[p];
                 if (D.slope) slv[j] = gp(D.slope)[p];
@@ -1173,8 +1179,9 @@ __device__ __forceinline__ void cut_tile(const StepParams &P, const InstDesc &D,
     int hx, hy;
     G::ring(min(tid, G::RING - 1), hx, hy);
     const bool hin = x0 + hx - 1 >= 0 && x0 + hx - 1 < W && y0 + hy - 1 >= 0 && y0 + hy - 1 < H;
-    const int hq = min(max(y0 + hy - 1, 0), H - 1) * W + min(max(x0 + hx - 1, 0), W - 1);
-    const int hrm = ldc<COH>(&gp(D.rmask)[hq]);
+    const int hqy = min(max(y0 + hy - 1, 0), H - 1), hqx = min(max(x0 + hx - 1, 0), W - 1);
+    const int hq = hqy * W + hqx;
+    const int hrm = ldc<COH>(&gp(D.rmask)[hqy * WP + hqx]);
     const int hmk = first ? ((hrm & kEBit) ? 1 : 0) : ldc<COH>(&mask[hq]);
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
@@ -1189,7 +1196,7 @@ __device__ __forceinline__ void cut_tile(const StepParams &P, const InstDesc &D,
             // the pixel from the mask in its next pass
             const int sl = sdv[j] == 0 ? slv[j] : 0;
             if (dlam > 0 && sl > 0) {
-                const int p = (y0 + ly0 + j * RPI) * W + x0 + lx;
+                const int p = (y0 + ly0 + j * RPI) * WP + x0 + lx;
                 const int ne = ev[j] - sl * dlam;
                 stc<COH>(&gp(D.e)[p], ne);
                 const int rm = (rmv[j] & ~(kRtBit | kEBit)) | x_bits(ne);
