@@ -700,7 +700,8 @@ int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_
         int &egrid = h->engine_grid[kset == 4 ? 0 : kset == 8 ? 1 : 2];
         if (egrid == 0) egrid = std::max(1, engine_workgroups(h->tw, kset));
         if (hipEventRecord(h->ev0, s) != hipSuccess) return PMF_EDEVICE;
-        if (launch_engine(P, E, h->tw, kset, std::min(egrid, P.ntiles), s) != 0) return PMF_EDEVICE;
+        E.wgs = std::min(egrid, P.ntiles);
+        if (launch_engine(P, E, h->tw, kset, s) != 0) return PMF_EDEVICE;
         if (hipEventRecord(h->ev1, s) != hipSuccess) return PMF_EDEVICE;
         if (hipMemcpyAsync(h->pinned + 63, E.rounds, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return PMF_EDEVICE;
         h->stats.work_launches += 1;

@@ -181,6 +181,7 @@ struct EngineParams {
     int32_t *sync;        // [work list][kEngSync] claim, done and info words
     int32_t avail_words;  // a multiple of 16
     int32_t quota;
+    int32_t wgs;          // workgroups of the launch
 };
 constexpr int kEngSync = 96;  // words of an instance's three lines
 enum { kSyClaim = 0, kSyDone = 32, kSyInfo = 64 };
@@ -196,7 +197,7 @@ constexpr int kEngineTiles = 640;     // tiles of the largest instance it is use
 // runtime cannot tell); kset: 4 or 8 when every instance of the work list has
 // that connectivity, 12 for a mixed list.
 int engine_workgroups(int tile_w, int kset);
-int launch_engine(const StepParams &p, const EngineParams &e, int tile_w, int kset, int grid, void *stream);
+int launch_engine(const StepParams &p, const EngineParams &e, int tile_w, int kset, void *stream);
 
 // out[p] (+)= number of the L masks that hold pixel p (n pixels).
 int launch_levels(const uint8_t *masks, int L, int n, uint8_t *out, bool accumulate, void *stream);
