@@ -113,7 +113,8 @@ BlockLayout block_layout(const pmf_instance &I, int tw, int th, bool gap) {
 // at least 512 bytes, so the pool can never hold more tiles than this.
 size_t worklist_cap(int slots, size_t pool_bytes) { return pool_bytes / 512 + (size_t)slots; }
 
-// The device-driven solve keeps an instance's tile list (4 bytes per tile) in the list memory, whose 32 bytes per work-list
+// The device-driven solve keeps an instance's tile list (4 bytes per tile) in
+// the list memory, whose 32 bytes per work-list
 // entry are dealt out by the instance's place in the pool: the block at
 // [off, off + bytes) owns the 64-byte lines [engine_list_at(off), engine_list_at(off +
 // bytes)).  A block of one tile has at least 2816 bytes and every further
@@ -224,8 +225,25 @@ struct pmf_handle {
     size_t arena_bytes = 0;
     bool own_arena = true;
     int32_t *pinned = nullptr;  // host-visible copy of the counter block (completions, list sizes, barrier)
-    int32_t *pinned_ring = nullptr;
-    InstState *pinned_state = nullptr;
+    // host copy of what a wait reads back, laid out as on the device: the
+    // states, the completion ring and the counter block; pinned memory that
+    // every handle has from the start and grows (`poll`), or, when it must not
+    // grow, an ordinary vector
+    char *poll = nullptr;
+    size_t poll_cap = 0, poll_bytes = 0;
+    bool poll_pinned = false;
+    InstState *state_host = nullptr;
+    int32_t *ring_host = nullptr;
+    int32_t *cnt_host = nullptr;
+    std::vector<char> host_poll;
+    // a batch being set up: the host image of its control area (from the
+    // descriptors to the chunk table), copied to the device in one piece
+    char *image = nullptr;
+    size_t image_bytes = 0;
+    char *stage = nullptr;  // pinned memory for it
+    size_t stage_cap = 0;
+    std::vector<char> host_image;  // and the ordinary memory of an image too large for that
+    bool rounds_clean = false;     // the superstep count in the counter block is zero
     // session
     bool open = false;
     int max_slots = 0;
@@ -279,13 +297,10 @@ struct pmf_handle {
     StepParams *P_dev = nullptr;          // device copy of P read by the persistent launch
     StepParams *pinned_params = nullptr;  // its staging copy
     // device memory the current session is laid out in: the arena, or memory
-    // handed in for one solve (then polled through host vectors instead of
-    // the pinned buffers, so that the solve allocates nothing)
+    // handed in for one solve (nothing is then allocated on the device or pinned)
     char *base = nullptr;
     bool ext = false;
     char *scratch_dev = nullptr;
-    std::vector<int32_t> host_ring;
-    std::vector<InstState> host_state;
     std::vector<int32_t> user_first, user_L;
 };
 
@@ -331,13 +346,38 @@ int ensure_arena(pmf_handle *h, size_t need) {
     return PMF_OK;
 }
 
+// Pinned host memory of at least `need` bytes in *p (capacity *cap): kept,
+// or replaced by a larger piece once the stream is idle.
+bool ensure_pinned(char **p, size_t *cap, size_t need) {
+    if (need <= *cap) return true;
+    if (*p) (void)hipHostFree(*p);
+    *p = nullptr;
+    *cap = 0;
+    const size_t want = need + need / 4;
+    if (hipHostMalloc((void **)p, want, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        *p = nullptr;
+        return false;
+    }
+    *cap = want;
+    return true;
+}
+
+// Images and waits of up to this many bytes go through pinned memory in one
+// copy; every handle has pinned memory for small ones from the start.
+constexpr size_t kBulkBytes = (size_t)1 << 20, kHostWords = (size_t)64 << 10;
+
 // Lay out the control area at the start of the arena and the pool after it
 // (or at the start of `ext_base`, ext_bytes of device memory handed in for
-// one solve, which must hold both: PMF_ENOMEM otherwise; host buffers for
-// polling are then ordinary host memory).
-int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = nullptr, size_t ext_bytes = 0) {
+// one solve, which must hold both: PMF_ENOMEM otherwise; no host memory is
+// then pinned either).  With table_bytes >= 0 a batch is set up: its slots,
+// work list and the first table_bytes of the pool are written to h->image and
+// go to the device with upload_image; otherwise every slot starts idle here.
+int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = nullptr, size_t ext_bytes = 0,
+                 int64_t table_bytes = -1) {
     if (slots < 1) return PMF_EINVAL;
     h->open = false;  // a captured graph stays: it is replayed only while the parameters match
+    h->image = nullptr;
     (void)hipStreamSynchronize(h->stream);
     const size_t wl = worklist_cap(slots, pool_bytes);
     const size_t ctl = control_bytes(slots, wl);
@@ -347,26 +387,21 @@ int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = n
         if (ctl + pool_bytes > ext_bytes) return PMF_ENOMEM;
         h->base = ext_base;
         base_bytes = ext_bytes;
-        h->host_ring.resize(slots);
-        h->host_state.resize(slots);
     } else {
         int rc = ensure_arena(h, ctl + pool_bytes + h->reserve_tail);
         if (rc != PMF_OK) return rc;
         h->base = h->arena;
         base_bytes = h->arena_bytes - h->reserve_tail;
     }
-    if (!h->ext && ((int)h->slots.size() < slots || !h->pinned_ring)) {
-        if (h->pinned_state) (void)hipHostFree(h->pinned_state);
-        if (h->pinned_ring) (void)hipHostFree(h->pinned_ring);
-        h->pinned_state = nullptr;
-        h->pinned_ring = nullptr;
-        if (hipHostMalloc((void **)&h->pinned_ring, 4 * (size_t)slots, hipHostMallocDefault) != hipSuccess ||
-            hipHostMalloc((void **)&h->pinned_state, sizeof(InstState) * (size_t)slots, hipHostMallocDefault) !=
-                hipSuccess) {
-            (void)hipGetLastError();
-            return PMF_ENOMEM;
-        }
-    }
+    const size_t b_st = align_up(sizeof(InstState) * (size_t)slots), b_ring = align_up(4 * (size_t)slots);
+    h->poll_bytes = b_st + b_ring + align_up(256);
+    if (!h->ext && !ensure_pinned(&h->poll, &h->poll_cap, h->poll_bytes)) return PMF_ENOMEM;
+    h->poll_pinned = h->poll_bytes <= h->poll_cap;
+    if (!h->poll_pinned) h->host_poll.resize(h->poll_bytes);
+    char *poll = h->poll_pinned ? h->poll : h->host_poll.data();
+    h->state_host = (InstState *)poll;
+    h->ring_host = (int32_t *)(poll + b_st);
+    h->cnt_host = (int32_t *)(poll + b_st + b_ring);
     char *A = h->base;
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -376,13 +411,15 @@ int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = n
     };
     StepParams &P = h->P;
     std::memset(&P, 0, sizeof(P));
+    P.lists = (int32_t *)take(4 * 8 * wl);
+    h->P_dev = (StepParams *)take(sizeof(StepParams));
+    // these five are one copy to the device when a batch starts, and the
+    // states, the ring and the counter block one copy back after each launch
     P.desc = (InstDesc *)take(sizeof(InstDesc) * (size_t)slots);
     P.st = (InstState *)take(sizeof(InstState) * (size_t)slots);
     P.ring = (int32_t *)take(4 * (size_t)slots);
     P.ring_count = (int32_t *)take(256);
     P.wl_slot = (const int32_t *)take(4 * (size_t)slots);
-    P.lists = (int32_t *)take(4 * 8 * wl);
-    h->P_dev = (StepParams *)take(sizeof(StepParams));
     P.list_count = P.ring_count + 4;  // counter block: [0] ring, [4..11] lists
     P.list_cap = (int32_t)wl;
     P.ring_cap = slots;
@@ -417,11 +454,42 @@ int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = n
     h->trace.clear();
     h->stats.device_bytes = (int64_t)base_bytes;
     // every slot starts idle; the completion counter at zero
+    h->rounds_clean = true;
+    if (table_bytes >= 0) {
+        h->image_bytes = h->pool_base + (size_t)table_bytes - (size_t)((char *)P.desc - A);
+        const bool pin = h->image_bytes <= h->stage_cap ||
+                         (!h->ext && h->image_bytes <= kBulkBytes &&
+                          ensure_pinned(&h->stage, &h->stage_cap, h->image_bytes));
+        if (!pin) h->host_image.resize(h->image_bytes);
+        h->image = pin ? h->stage : h->host_image.data();
+        std::memset(h->image, 0, h->image_bytes);
+        h->open = true;
+        return PMF_OK;
+    }
     if (hipMemsetAsync(P.st, 0, sizeof(InstState) * (size_t)slots, h->stream) != hipSuccess ||
         hipMemsetAsync(P.ring_count, 0, 256, h->stream) != hipSuccess)
         return PMF_EDEVICE;
     h->open = true;
     return PMF_OK;
+}
+
+// Where the batch's image holds the device address `dev`.
+template <class T>
+T *in_image(pmf_handle *h, T *dev) {
+    return (T *)(h->image + ((const char *)dev - (const char *)h->P.desc));
+}
+
+// The image to the device.  Pinned memory stays as it is until the solve's
+// first wait; ordinary memory is given back once it is copied.
+int upload_image(pmf_handle *h) {
+    const char *src = h->image;
+    h->image = nullptr;
+    if (hipMemcpyAsync(h->P.desc, src, h->image_bytes, hipMemcpyHostToDevice, h->stream) != hipSuccess)
+        return PMF_EDEVICE;
+    if (src == h->stage) return PMF_OK;
+    const bool ok = hipStreamSynchronize(h->stream) == hipSuccess;
+    std::vector<char>().swap(h->host_image);
+    return ok ? PMF_OK : PMF_EDEVICE;
 }
 
 // Rebuild the work list: every tile of every admitted, unfinished instance,
@@ -451,7 +519,9 @@ int rebuild_worklist(pmf_handle *h) {
     P.nwl = (int32_t)ids.size();
     P.wl_ident = 1;
     for (size_t w = 0; w < ids.size(); ++w) P.wl_ident &= ids[w] == (int)w ? 1 : 0;
-    if (!ids.empty()) {
+    if (h->image) {
+        std::copy(ids.begin(), ids.end(), (int32_t *)in_image(h, P.wl_slot));
+    } else if (!ids.empty()) {
         std::vector<int32_t> wl(ids.begin(), ids.end());
         if (hipMemcpyAsync((void *)P.wl_slot, wl.data(), 4 * wl.size(), hipMemcpyHostToDevice, h->stream) !=
             hipSuccess)
@@ -486,8 +556,11 @@ int submit(pmf_handle *h, const pmf_instance *inst, int n, int64_t *flows_out, i
         for (int i = 0; i < got; ++i) h->pool.release(offs[i], lay[i].total);
         return PMF_EBUSY;
     }
-    std::vector<InstDesc> desc(n);
-    std::vector<InstState> st(n);
+    // a batch writes its slots (0, 1, 2, ... of a fresh session) to its image
+    std::vector<InstDesc> desc_v(h->image ? 0 : n);
+    std::vector<InstState> st_v(h->image ? 0 : n);
+    InstDesc *desc = h->image ? in_image(h, h->P.desc) : desc_v.data();
+    InstState *st = h->image ? in_image(h, h->P.st) : st_v.data();
     std::vector<int> ids(n);
     int64_t lam_base = 0;
     for (int i = 0; i < n; ++i) {
@@ -551,6 +624,8 @@ int submit(pmf_handle *h, const pmf_instance *inst, int n, int64_t *flows_out, i
         s.masks = h->pool_base + offs[i] + B.masks;
         if (ids_out) ids_out[i] = id;
     }
+    if (n) h->wl_dirty = true;
+    if (h->image) return PMF_OK;
     // descriptors and states go to their slots, one copy per run of
     // consecutive ids (ids need not be contiguous; a fresh batch is one run)
     for (int i = 0; i < n;) {
@@ -565,7 +640,6 @@ int submit(pmf_handle *h, const pmf_instance *inst, int n, int64_t *flows_out, i
         i = j;
     }
     if (hipStreamSynchronize(h->stream) != hipSuccess) return PMF_EDEVICE;
-    if (n) h->wl_dirty = true;
     return PMF_OK;
 }
 
@@ -653,9 +727,27 @@ bool engine_usable(pmf_handle *h) {
     return true;
 }
 
+// Workgroups of the device-driven launch, by work-list connectivity.
+int engine_wgs(pmf_handle *h, int kset) {
+    int &g = h->engine_grid[kset == 4 ? 0 : kset == 8 ? 1 : 2];
+    if (g == 0) g = engine_workgroups(h->tw, kset);
+    return g;
+}
+
+// What a batch's chunks come to: its instances' statuses (device pointers).
+struct BatchEnd {
+    const int32_t *sub_status;
+    const int64_t *meta;
+    int n_user;
+    int64_t *flows;
+    int32_t *status;
+    bool queued;  // the combining kernel runs behind the last launch
+};
+
 // Launch `steps` supersteps (or, in the latency-bound tail, one persistent
 // launch of up to `persist_steps`), wait, and collect the slots that finished.
-int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_steps = 0) {
+int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_steps = 0,
+              BatchEnd *end = nullptr) {
     if (h->poisoned) return PMF_EDEVICE;
     if (h->wl_dirty) {
         const int rc = rebuild_worklist(h);
@@ -693,18 +785,24 @@ int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_
         EngineParams E;
         E.avail_words = engine_words(P.nwl);
         E.live = (int32_t *)h->engine_mem;
-        E.rounds = E.live + 8 * 32;
-        E.avail = (unsigned long long *)(E.rounds + 32);
+        E.rounds = P.ring_count + kBarRounds;
+        E.avail = (unsigned long long *)(E.live + 8 * 32);
         E.sync = (int32_t *)(h->engine_mem + engine_clear_bytes(E.avail_words));
         E.quota = std::max(steps, persist_steps);
-        int &egrid = h->engine_grid[kset == 4 ? 0 : kset == 8 ? 1 : 2];
-        if (egrid == 0) egrid = std::max(1, engine_workgroups(h->tw, kset));
+        if (!h->rounds_clean && hipMemsetAsync(E.rounds, 0, 4, s) != hipSuccess) return PMF_EDEVICE;
+        h->rounds_clean = false;
         if (hipEventRecord(h->ev0, s) != hipSuccess) return PMF_EDEVICE;
-        E.wgs = std::min(egrid, P.ntiles);
+        E.wgs = std::min(std::max(1, engine_wgs(h, kset)), P.ntiles);
         if (launch_engine(P, E, h->tw, kset, s) != 0) return PMF_EDEVICE;
         if (hipEventRecord(h->ev1, s) != hipSuccess) return PMF_EDEVICE;
-        if (hipMemcpyAsync(h->pinned + 63, E.rounds, 4, hipMemcpyDeviceToHost, s) != hipSuccess) return PMF_EDEVICE;
         h->stats.work_launches += 1;
+        // almost always the batch's last launch: the statuses are combined
+        // right behind it and one wait is enough
+        if (end) {
+            if (launch_finalize(end->sub_status, end->meta, end->n_user, end->flows, end->status, s) != 0)
+                return PMF_EDEVICE;
+            end->queued = true;
+        }
     }
     if (P.ntiles > 0 && !persisted && !engine) {
         // replay a captured graph: a batch's work list from its first superstep
@@ -748,25 +846,25 @@ int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_
         h->stats.supersteps += steps;
         h->epoch_steps += steps;
     }
-    // A batch (few slots, all admitted at once) copies the whole completion
-    // ring and every slot's state along with the completion count: one round
-    // trip per sync instead of two and a copy per finished instance.
+    // A batch (few slots, all admitted at once) copies every slot's state and
+    // the whole completion ring along with the counter block: one copy and
+    // one wait instead of a copy per finished instance.
     const int cap = h->max_slots;
-    const bool bulk = h->batch && !h->ext && (size_t)cap * sizeof(InstState) <= ((size_t)1 << 20);
-    int32_t *ringb = h->ext ? h->host_ring.data() : h->pinned_ring;
-    InstState *stateb = h->ext ? h->host_state.data() : h->pinned_state;
+    const bool bulk = h->batch && h->poll_pinned && h->poll_bytes <= kBulkBytes;
+    int32_t *ringb = h->ring_host;
+    InstState *stateb = h->state_host;
     // device-to-host copy of polled data: queued on the stream into pinned
-    // memory, or (memory handed in: ordinary host memory) synchronous once
-    // the stream is idle
+    // memory, or (ordinary host memory) synchronous once the stream is idle
     auto d2h = [&](void *dst, const void *src, size_t bytes) -> bool {
-        if (h->ext) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) == hipSuccess;
+        if (!h->poll_pinned) return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) == hipSuccess;
         return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s) == hipSuccess;
     };
     // the counter block: completions, list sizes of the last superstep, barrier words
-    if (hipMemcpyAsync(h->pinned, P.ring_count, 4 * (kBarSteps + 1), hipMemcpyDeviceToHost, s) != hipSuccess)
+    if (bulk) {
+        if (!d2h(stateb, P.st, h->poll_bytes)) return PMF_EDEVICE;
+    } else if (hipMemcpyAsync(h->pinned, P.ring_count, 4 * (kBarRounds + 1), hipMemcpyDeviceToHost, s) != hipSuccess) {
         return PMF_EDEVICE;
-    if (bulk && (!d2h(ringb, P.ring, 4 * (size_t)cap) || !d2h(stateb, P.st, sizeof(InstState) * (size_t)cap)))
-        return PMF_EDEVICE;
+    }
     if (hipStreamSynchronize(s) != hipSuccess) return PMF_EDEVICE;
     h->stats.host_syncs += 1;
     if (P.ntiles > 0) {
@@ -782,7 +880,7 @@ int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_
         if (timing && hipMemcpy(h->stats.kernel_px, h->kpx, 16 * sizeof(int64_t), hipMemcpyDeviceToHost) != hipSuccess)
             return PMF_EDEVICE;
     }
-    const volatile int32_t *cb = h->pinned;
+    const volatile int32_t *cb = bulk ? h->cnt_host : h->pinned;
     if (persisted) {
         if (cb[kBarAbort] != 0) {
             h->poisoned = true;  // a superstep was left half done
@@ -794,8 +892,8 @@ int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_
         h->epoch_steps += ran;
     }
     if (engine) {
-        h->stats.supersteps += cb[63];
-        h->epoch_steps += cb[63];
+        h->stats.supersteps += cb[kBarRounds];
+        h->epoch_steps += cb[kBarRounds];
     }
     if (P.ntiles > 0) h->last_listed = (int64_t)cb[8] + cb[9] + cb[10] + cb[11];
     const int32_t count = cb[0];
@@ -927,6 +1025,7 @@ int pmf_create(const pmf_options *opt, void *stream, void *workspace, size_t ws_
     }
     if (hipHostMalloc((void **)&h->pinned, 256, hipHostMallocDefault) != hipSuccess ||
         hipHostMalloc((void **)&h->pinned_params, sizeof(StepParams), hipHostMallocDefault) != hipSuccess ||
+        !ensure_pinned(&h->poll, &h->poll_cap, kHostWords) || !ensure_pinned(&h->stage, &h->stage_cap, kHostWords) ||
         hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreate(&h->ev0) != hipSuccess || hipEventCreate(&h->ev1) != hipSuccess) {
         (void)hipGetLastError();
@@ -1036,7 +1135,7 @@ int64_t batch_tiles(const pmf_instance *inst, int n, int C, int tw, int th, int6
 int longest_parallel_chunk(pmf_handle *h, const pmf_instance *inst, int n, int C, int maxL) {
     int64_t t8 = 0;
     const int64_t t = batch_tiles(inst, n, 1, h->tw, h->th, &t8);
-    const int res = engine_workgroups(h->tw, 2 * t8 >= t ? 8 : 4);
+    const int res = engine_wgs(h, 2 * t8 >= t ? 8 : 4);
     if (res <= 0) return C;
     const int64_t target = kTilesPerWorkgroup * res;
     while (C < maxL && batch_tiles(inst, n, C + 1, h->tw, h->th, nullptr) >= target) ++C;
@@ -1048,6 +1147,7 @@ int choose_chunk(pmf_handle *h, const pmf_instance *inst, int n, size_t ext_byte
     for (int i = 0; i < n; ++i) maxL = std::max(maxL, (int)inst[i].L);
     if (h->opt.lambda_chunk > 0) return std::min((int)h->opt.lambda_chunk, maxL);
     size_t budget;
+    bool known = true;
     if (ext_bytes) {
         budget = ext_bytes;
     } else if (!h->own_arena) {
@@ -1055,15 +1155,24 @@ int choose_chunk(pmf_handle *h, const pmf_instance *inst, int n, size_t ext_byte
     } else if (h->opt.mem_budget > 0) {
         budget = (size_t)h->opt.mem_budget;
     } else {
-        size_t fr = 0, tot = 0;
-        if (hipMemGetInfo(&fr, &tot) != hipSuccess) return maxL;
-        budget = (size_t)((double)(fr + h->arena_bytes) * 0.7);
+        // of the free memory and the arena; a layout that fits into this share
+        // of the arena alone needs no look at the free memory
+        budget = (size_t)((double)h->arena_bytes * 0.7);
+        known = false;
     }
     for (int C = 1;; C = C < 4 ? C + 1 : C * 2) {
         if (C >= maxL) return maxL;
         int64_t subs = 0;
         const size_t pool = batch_pool_bytes(inst, n, C, h->tw, h->th, h->opt.gap != 0, &subs);
-        if (subs <= (1 << 20) && pool + control_bytes((int)subs, worklist_cap((int)subs, pool)) <= budget)
+        if (subs > (1 << 20)) continue;
+        const size_t need = pool + control_bytes((int)subs, worklist_cap((int)subs, pool));
+        if (need > budget && !known) {
+            size_t fr = 0, tot = 0;
+            if (hipMemGetInfo(&fr, &tot) != hipSuccess) return maxL;
+            budget = (size_t)((double)(fr + h->arena_bytes) * 0.7);
+            known = true;
+        }
+        if (need <= budget)
             return longest_parallel_chunk(h, inst, n, C, maxL);
     }
 }
@@ -1094,17 +1203,12 @@ int solve_batch(pmf_handle *h, const pmf_instance *inst, int32_t n_inst, int64_t
     const int C = n_inst ? choose_chunk(h, inst, n_inst, ext_base ? ext_bytes : 0) : 1;
     int64_t n_sub = 0;
     const size_t pool = batch_pool_bytes(inst, n_inst, C, h->tw, h->th, h->opt.gap != 0, &n_sub);
-    rc = open_session(h, (int)std::max<int64_t>(n_sub, 1), pool, ext_base, ext_bytes);
-    if (rc != PMF_OK) return rc;
-    h->batch = true;
-    h->chunk = C;
-    h->user_first.assign(n_inst + 1, 0);
-    h->user_L.assign(n_inst, 0);
-    if (n_inst == 0) return PMF_OK;
     // chunks in caller order, so that their flows are contiguous in flows_out
     std::vector<pmf_instance> subs;
     std::vector<uint8_t> prev;
     std::vector<int64_t> meta(3 * (size_t)n_inst + 1);
+    h->user_first.assign(n_inst + 1, 0);
+    h->user_L.assign(n_inst, 0);
     int64_t foff = 0;
     for (int i = 0; i < n_inst; ++i) {
         h->user_first[i] = (int32_t)subs.size();
@@ -1123,17 +1227,29 @@ int solve_batch(pmf_handle *h, const pmf_instance *inst, int32_t n_inst, int64_t
     }
     meta[n_inst] = (int64_t)subs.size();
     h->user_first[n_inst] = (int32_t)subs.size();
-    // the finalize metadata takes the first pool block
+    // the chunk table and the chunks' statuses take the first pool block; an
+    // instance of one chunk has that chunk's status, so when all are, the
+    // chunks write the caller's statuses themselves
+    const bool chunked = subs.size() > (size_t)n_inst;
+    const size_t tbytes = chunked ? align_up(8 * meta.size()) : 0;
+    const size_t mbytes = chunked ? tbytes + align_up(4 * subs.size()) : 0;
+    rc = open_session(h, (int)std::max<int64_t>(n_sub, 1), pool, ext_base, ext_bytes,
+                      n_inst ? (int64_t)mbytes : (int64_t)-1);
+    if (rc != PMF_OK) return rc;
+    h->batch = true;
+    h->chunk = C;
+    if (n_inst == 0) return PMF_OK;
     size_t moff = 0;
-    const size_t mbytes = align_up(8 * meta.size()) + align_up(4 * subs.size());
-    if (!h->pool.alloc(mbytes, &moff)) return PMF_ENOMEM;
+    if (mbytes && !h->pool.alloc(mbytes, &moff)) return PMF_ENOMEM;
     char *mbase = h->base + h->pool_base + moff;
-    int64_t *d_meta = (int64_t *)mbase;
-    int32_t *d_sub_status = (int32_t *)(mbase + align_up(8 * meta.size()));
-    if (hipMemcpyAsync(d_meta, meta.data(), 8 * meta.size(), hipMemcpyHostToDevice, h->stream) != hipSuccess)
-        return PMF_EDEVICE;
-    rc = submit(h, subs.data(), (int)subs.size(), flows_out, d_sub_status, nullptr, prev.data());
+    BatchEnd end{(const int32_t *)(mbase + tbytes), (const int64_t *)mbase, n_inst, flows_out, status_out, false};
+    if (chunked) std::memcpy(in_image(h, mbase), meta.data(), 8 * meta.size());
+    rc = submit(h, subs.data(), (int)subs.size(), flows_out, chunked ? (int32_t *)(mbase + tbytes) : status_out,
+                nullptr, prev.data());
+    if (rc == PMF_OK) rc = rebuild_worklist(h);
+    const int up = upload_image(h);
     if (rc != PMF_OK) return rc == PMF_EBUSY ? PMF_ENOMEM : rc;
+    if (up != PMF_OK) return up;
     // The work list keeps finished instances (their tiles exit at once), so
     // one captured superstep graph serves the whole solve.
     const int S = h->opt.steps_per_sync;
@@ -1143,12 +1259,14 @@ int solve_batch(pmf_handle *h, const pmf_instance *inst, int32_t n_inst, int64_t
     for (int64_t round = 0; done < (int64_t)subs.size(); ++round) {
         if (round > max_rounds) return PMF_ETIMEOUT;
         fin.clear();
-        rc = run_steps(h, S, &fin, 1 << 16);
+        end.queued = false;
+        rc = run_steps(h, S, &fin, 1 << 16, chunked ? &end : nullptr);
         if (rc != PMF_OK) return rc;
         done += (int64_t)fin.size();
         h->wl_dirty = false;
     }
-    if (launch_finalize(d_sub_status, d_meta, n_inst, flows_out, status_out, h->stream) != 0) return PMF_EDEVICE;
+    if (!chunked || end.queued) return PMF_OK;
+    if (launch_finalize(end.sub_status, end.meta, n_inst, flows_out, status_out, h->stream) != 0) return PMF_EDEVICE;
     if (hipStreamSynchronize(h->stream) != hipSuccess) return PMF_EDEVICE;
     return PMF_OK;
 }
@@ -1524,7 +1642,7 @@ int pmf_slot_stats(pmf_handle *h, int64_t *out, int32_t max_slots, int32_t *n_sl
         const Slot &s = h->slots[i];
         std::memset(o, 0, 8 * sizeof(int64_t));
         if (!s.live || !s.finished) continue;
-        const InstState &x = h->ext ? h->host_state[i] : h->pinned_state[i];
+        const InstState &x = h->state_host[i];
         o[0] = 1;
         o[1] = x.steps;
         o[2] = x.sweeps;
@@ -1908,8 +2026,8 @@ int pmf_destroy(pmf_handle *h) {
     if (h->engine_mem) (void)hipFree(h->engine_mem);
     if (h->pinned) (void)hipHostFree(h->pinned);
     if (h->pinned_params) (void)hipHostFree(h->pinned_params);
-    if (h->pinned_ring) (void)hipHostFree(h->pinned_ring);
-    if (h->pinned_state) (void)hipHostFree(h->pinned_state);
+    if (h->poll) (void)hipHostFree(h->poll);
+    if (h->stage) (void)hipHostFree(h->stage);
     if (h->capture) (void)hipStreamDestroy(h->capture);
     if (h->ev0) (void)hipEventDestroy(h->ev0);
     if (h->ev1) (void)hipEventDestroy(h->ev1);

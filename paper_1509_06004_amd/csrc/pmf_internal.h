@@ -165,6 +165,7 @@ int launch_superstep(const StepParams &p, int tile_w, void *stream, void *const 
 // kset: 4 or 8 when every instance of the work list has that connectivity,
 // 12 for a mixed list.  Not for the gap heuristic.
 constexpr int kBarAbort = 18, kBarSteps = 19;
+constexpr int kBarRounds = 24;  // device-driven solve: EngineParams::rounds
 int persist_workgroups(int tile_w, int kset);
 int launch_persist(const StepParams *p_dev, int tile_w, int kset, int grid, int max_steps, int exit_tiles,
                    void *stream);
@@ -176,7 +177,7 @@ int launch_persist(const StepParams *p_dev, int tile_w, int kset, int grid, int 
 // 64-byte line at which the instance's share starts.
 struct EngineParams {
     int32_t *live;        // [8 * 32] per XCD: tiles of the instances still running (one word per 128 bytes)
-    int32_t *rounds;      // most supersteps an instance ran in this launch
+    int32_t *rounds;      // most supersteps an instance ran in this launch (a word of the counter block)
     unsigned long long *avail;  // [8][avail_words] per XCD: a bit per work-list entry with unclaimed tiles
     int32_t *sync;        // [work list][kEngSync] claim, done and info words
     int32_t avail_words;  // a multiple of 16
@@ -187,7 +188,7 @@ constexpr int kEngSync = 96;  // words of an instance's three lines
 enum { kSyClaim = 0, kSyDone = 32, kSyInfo = 64 };
 enum { kInPhase, kInSwap, kInSub, kInK, kInReps, kInXsw, kInLeft, kEngInfo };
 constexpr int kEngLine = 16;  // words of a line of the list memory
-constexpr size_t engine_clear_bytes(int avail_words) { return 8 * 128 + 128 + 8 * (size_t)avail_words * 8; }
+constexpr size_t engine_clear_bytes(int avail_words) { return 8 * 128 + 8 * (size_t)avail_words * 8; }
 constexpr int engine_words(int n) { return (n + 1023) / 1024 * 16; }
 constexpr size_t engine_bytes(int n) { return engine_clear_bytes(engine_words(n)) + (size_t)n * kEngSync * 4; }
 constexpr int kEngineSlots = 4096;    // instances that every handle has room for from the start
