@@ -1334,27 +1334,36 @@ int integer_breakpoints(pmf_handle *h, const pmf_instance &base, int32_t lam_lo,
         I.lambdas = dl;
         rc = pmf_solve_batch(h, &I, 1, df, ds);
         if (rc != PMF_OK) return rc;
-        int32_t st = PMF_OK;
-        if (hipMemcpy(&st, ds, 4, hipMemcpyDeviceToHost) != hipSuccess) return PMF_EDEVICE;
-        if (st != PMF_OK) return st;
-        for (int i = 0; i < m; ++i) {
-            int slot, k;
-            rc = locate(h, 0, i, &slot, &k);
-            if (rc != PMF_OK) return rc;
-            const uint8_t *mask = (const uint8_t *)(h->base + h->slots[slot].masks + (size_t)k * n);
-            if (launch_mask_stats(mask, n, base.snk_slope, base.seed, dst + 2 * i, h->stream) != 0) return PMF_EDEVICE;
-            if (exit_out && launch_exit_min(mask, n, lams[i], exit_out, h->stream) != 0) return PMF_EDEVICE;
+        // (a failed solve's masks are read as well: memory of the arena, and
+        // its status ends the search before anything that came of them is used)
+        for (int i0 = 0; i0 < m; i0 += kProbeMasks) {
+            MaskTable t;
+            t.count = std::min(kProbeMasks, m - i0);
+            for (int i = 0; i < t.count; ++i) {
+                int slot, k;
+                rc = locate(h, 0, i0 + i, &slot, &k);
+                if (rc != PMF_OK) return rc;
+                t.mask[i] = (const uint8_t *)(h->base + h->slots[slot].masks + (size_t)k * n);
+                t.lam[i] = lams[i0 + i];
+            }
+            if (launch_level_stats(t, n, base.snk_slope, base.seed, dst + 2 * i0, exit_out, h->stream) != 0)
+                return PMF_EDEVICE;
         }
-        std::vector<int64_t> f(m), sw(2 * (size_t)m);
-        if (hipMemcpyAsync(f.data(), df, 8 * (size_t)m, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
-            hipMemcpyAsync(sw.data(), dst, 16 * (size_t)m, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
+        std::vector<char> back(T - o_f);  // flows, status, sums
+        if (hipMemcpyAsync(back.data(), df, T - o_f, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
             hipStreamSynchronize(h->stream) != hipSuccess)
             return PMF_EDEVICE;
-        for (int i = 0; i < m; ++i) {
+        int32_t st = PMF_OK;
+        std::memcpy(&st, back.data() + (o_s - o_f), 4);
+        if (st != PMF_OK) return st;
+        const int64_t *f = (const int64_t *)back.data(), *sums = (const int64_t *)(back.data() + (o_st - o_f));
+        int64_t size = 0, w = 0;
+        for (int i = m - 1; i >= 0; --i) {
+            if ((i + 1) % kProbeMasks == 0) size = w = 0;  // the last set of a launch
             BpPoint &q = pts[lams[i]];
             q.F = f[i];
-            q.size = sw[2 * i];
-            q.w = sw[2 * i + 1];
+            q.size = size += sums[2 * i];
+            q.w = w += sums[2 * i + 1];
         }
         return PMF_OK;
     };
@@ -1752,20 +1761,20 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
             hipStreamSynchronize(h->stream) != hipSuccess)
             return release(PMF_EDEVICE);
     }
-    struct Interval {
+    struct Piece {
         int32_t c;
         int x0, y0, w, h;
         int64_t a;
-        size_t o_planes, o_ep, o_eq, o_stats;
-        int64_t st[kCsCount];
+        size_t o_planes, o_ep, o_eq;
+        const int64_t *st;
         Line fix;  // full-problem line = contracted line + fix
     };
-    std::vector<Interval> iv(k);
+    std::vector<Piece> iv(k);
     size_t P = 0;
     int64_t amax = 0;
     int wmax = 0, hmax = 0;
     for (int i = 0; i < k; ++i) {
-        Interval &I = iv[i];
+        Piece &I = iv[i];
         I.c = changes[i];
         I.x0 = box[4 * i];
         I.y0 = box[4 * i + 1];
@@ -1779,12 +1788,12 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
         P = align_up(P + 4 * (size_t)I.a);
         I.o_eq = P;
         P = align_up(P + 4 * (size_t)I.a);
-        I.o_stats = P;
-        P = align_up(P + 8 * (size_t)kCsCount);
         amax = std::max(amax, I.a);
         wmax = std::max(wmax, I.w);
         hmax = std::max(hmax, I.h);
     }
+    const size_t o_stats = P;
+    P += 8 * (size_t)kCsStride * k;
     // 3. device memory: the contracted problems (kept to the end), then per
     // round up to R scaled copies with their lambdas, flows, statuses and set
     // statistics, and the pool of a batch of R probes of the largest box
@@ -1814,16 +1823,32 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
     int32_t *dl = (int32_t *)(scr + o_l), *ds = (int32_t *)(scr + o_s);
     int64_t *df = (int64_t *)(scr + o_f), *dst = (int64_t *)(scr + o_st);
     // 4. contract each interval's problem to its changing pixels
-    for (int i = 0; i < k; ++i) {
-        Interval &I = iv[i];
-        if (launch_contract(base.nlink, base.cap_src, base.cap_snk0, base.snk_slope, base.seed, W, H, K, exit_out,
-                            I.c, I.x0, I.y0, I.w, I.h, (int32_t *)(pers + I.o_planes), (int32_t *)(pers + I.o_ep),
-                            (int32_t *)(pers + I.o_eq), (int64_t *)(pers + I.o_stats), h->stream) != 0 ||
-            hipMemcpyAsync(I.st, pers + I.o_stats, 8 * (size_t)kCsCount, hipMemcpyDeviceToHost, h->stream) !=
-                hipSuccess)
+    // (and at the end place its pixels) in launches of up to kProbeMasks
+    auto table_of = [&](int i0, int i1, int *nmax) {
+        IntervalTable t{};
+        *nmax = 0;
+        for (int i = i0; i < i1; ++i) {
+            const Piece &I = iv[i];
+            t.iv[i - i0] = Interval{(int32_t *)(pers + I.o_planes), (int32_t *)(pers + I.o_ep),
+                                    (int32_t *)(pers + I.o_eq), I.c, I.x0, I.y0, I.w, I.h, 0, 0};
+            *nmax = std::max(*nmax, (int)I.a);
+        }
+        return t;
+    };
+    std::vector<int64_t> st_all((size_t)kCsStride * k);
+    for (int i0 = 0; i0 < k; i0 += kProbeMasks) {
+        const int i1 = std::min(k, i0 + kProbeMasks);
+        int nmax = 0;
+        const IntervalTable t = table_of(i0, i1, &nmax);
+        if (launch_contract(t, i1 - i0, nmax, base.nlink, base.cap_src, base.cap_snk0, base.snk_slope, base.seed, W, H, K,
+                            exit_out, (int64_t *)(pers + o_stats) + (size_t)kCsStride * i0, h->stream) != 0)
             return release(PMF_EDEVICE);
     }
-    if (hipStreamSynchronize(h->stream) != hipSuccess) return release(PMF_EDEVICE);
+    if (hipMemcpyAsync(st_all.data(), pers + o_stats, 8 * st_all.size(), hipMemcpyDeviceToHost, h->stream) !=
+            hipSuccess ||
+        hipStreamSynchronize(h->stream) != hipSuccess)
+        return release(PMF_EDEVICE);
+    for (int i = 0; i < k; ++i) iv[i].st = st_all.data() + (size_t)kCsStride * i;
     // the two end lines of an interval in the contracted problem: all of D
     // in the source set (cost sum c0 + lambda * sum slope) and none of it
     // (cost sum cs); the pixels fixed by the contraction add the same line
@@ -1841,7 +1866,7 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
     std::vector<Pair> pend;
     std::vector<Found> found;
     for (int i = 0; i < k; ++i) {
-        Interval &I = iv[i];
+        Piece &I = iv[i];
         if (I.st[kCsSeeds] != 0) return release(PMF_ERANGE);  // capacities at INF: no finite contraction
         const Line Lc{I.st[kCsSumC0], I.st[kCsSumSl]}, Rc{I.st[kCsSumCs], 0};
         Line Lf, Rf;
@@ -1855,18 +1880,18 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
     // set at x gives a new line M and the pairs (L, M) and (M, R).  F(x) and
     // S_min(x) come from the contracted problem with every capacity
     // multiplied by q, solved at the integer lambda p.
-    struct Probe {
+    struct Todo {
         Pair pr;
         int32_t p, q;
     };
     int64_t probes_total = 0;
     while (!pend.empty()) {
-        std::vector<Probe> todo;
+        std::vector<Todo> todo;
         for (const Pair &pr : pend) {
             const int64_t num = pr.R.a - pr.L.a, den = pr.L.w - pr.R.w;
             if (den <= 0 || num <= 0) return release(PMF_EDEVICE);
             const int64_t g = std::gcd(num, den), p = num / g, q = den / g;
-            const Interval &I = iv[pr.iv];
+            const Piece &I = iv[pr.iv];
             if ((__int128)p <= (__int128)(I.c - 1) * q || (__int128)p > (__int128)I.c * q)
                 return release(PMF_EDEVICE);
             if ((__int128)p * pr.rq > (__int128)pr.rp * q) return release(PMF_EDEVICE);  // past R's point
@@ -1879,7 +1904,7 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
                 (__int128)q * I.st[kCsMaxNl] > PMF_NLINK_MAX(K) ||
                 (__int128)q * I.st[kCsMaxC0] + (__int128)I.st[kCsMaxSl] * p > lim)
                 return release(PMF_ERANGE);
-            todo.push_back(Probe{pr, (int32_t)p, (int32_t)q});
+            todo.push_back(Todo{pr, (int32_t)p, (int32_t)q});
         }
         probes_total += (int64_t)todo.size();
         if (probes_total > ((int64_t)1 << 22)) return release(PMF_ETIMEOUT);
@@ -1887,14 +1912,19 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
         for (size_t b0 = 0; b0 < todo.size(); b0 += (size_t)R) {
             const int m = (int)std::min<size_t>((size_t)R, todo.size() - b0);
             std::vector<pmf_instance> pi((size_t)m);
-            std::vector<int32_t> lam((size_t)m), sts((size_t)m);
+            std::vector<int32_t> lam((size_t)m);
+            ProbeTable tab;
+            int runs = 0, nmax = 0;
             for (int j = 0; j < m; ++j) {
-                const Probe &pb = todo[b0 + j];
-                const Interval &I = iv[pb.pr.iv];
+                const Todo &pb = todo[b0 + j];
+                const Piece &I = iv[pb.pr.iv];
                 const int32_t *src = (const int32_t *)(pers + I.o_planes);
                 int32_t *dstp = (int32_t *)(scr + (size_t)j * probe_planes);
-                if (launch_scale(src, (int64_t)(K + 2) * I.a, pb.q, dstp, h->stream) != 0)
-                    return release(PMF_EDEVICE);
+                tab.probe[j] = Probe{src, (int32_t *)(pers + I.o_ep), (int32_t *)(pers + I.o_eq), nullptr, (int32_t)I.a,
+                                     pb.p, pb.q};
+                // the pending pairs keep their intervals' order
+                if (j == 0 || pb.pr.iv != todo[b0 + j - 1].pr.iv) tab.run[runs++] = j;
+                nmax = std::max(nmax, (int)I.a);
                 pmf_instance &Q = pi[j];
                 Q = base;
                 Q.W = I.w;
@@ -1908,6 +1938,9 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
                 Q.lambdas = dl + j;
                 lam[j] = pb.p;
             }
+            tab.run[runs] = m;
+            if (launch_scale(tab, m, nmax, K + 2, (int32_t *)scr, probe_planes / 4, h->stream) != 0)
+                return release(PMF_EDEVICE);
             {
                 // the batch must fit in front of the tail: a larger arena
                 // would be a new allocation, and the tail would move
@@ -1917,7 +1950,7 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
                     return release(PMF_ENOMEM);
             }
             if (hipMemcpyAsync(dl, lam.data(), 4 * (size_t)m, hipMemcpyHostToDevice, h->stream) != hipSuccess ||
-                hipMemsetAsync(dst, 0, 16 * (size_t)m, h->stream) != hipSuccess)
+                hipMemsetAsync(dst, 0, 8 * (size_t)m, h->stream) != hipSuccess)
                 return release(PMF_EDEVICE);
             // the contracted probes hold no seeds and are solved as given (the
             // orientation rule is tuned for seeded images)
@@ -1926,35 +1959,29 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
             rc = pmf_solve_batch(h, pi.data(), m, df, ds);
             h->opt.orientation = orient;
             if (rc != PMF_OK) return release(rc);
-            if (hipMemcpy(sts.data(), ds, 4 * (size_t)m, hipMemcpyDeviceToHost) != hipSuccess)
-                return release(PMF_EDEVICE);
-            for (int j = 0; j < m; ++j)
-                if (sts[j] != PMF_OK) return release(sts[j]);
             for (int j = 0; j < m; ++j) {
-                const Probe &pb = todo[b0 + j];
-                const Interval &I = iv[pb.pr.iv];
                 int slot, kk;
                 rc = locate(h, j, 0, &slot, &kk);
                 if (rc != PMF_OK) return release(rc);
-                const uint8_t *mask = (const uint8_t *)(h->base + h->slots[slot].masks + (size_t)kk * I.a);
-                if (launch_mask_stats(mask, (int)I.a, pi[j].snk_slope, nullptr, dst + 2 * j, h->stream) != 0 ||
-                    launch_exit_rational(mask, (int)I.a, pb.p, pb.q, (int32_t *)(pers + I.o_ep),
-                                         (int32_t *)(pers + I.o_eq), h->stream) != 0)
-                    return release(PMF_EDEVICE);
+                tab.probe[j].mask = (const uint8_t *)(h->base + h->slots[slot].masks + (size_t)kk * tab.probe[j].n);
             }
-            std::vector<int64_t> f((size_t)m), sw(2 * (size_t)m);
-            if (hipMemcpyAsync(f.data(), df, 8 * (size_t)m, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
-                hipMemcpyAsync(sw.data(), dst, 16 * (size_t)m, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
+            if (launch_probe_sets(tab, runs, nmax, K + 2, dst, h->stream) != 0) return release(PMF_EDEVICE);
+            std::vector<char> back(o_st + 8 * (size_t)m - o_f);  // flows, statuses, sums
+            if (hipMemcpyAsync(back.data(), df, back.size(), hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
                 hipStreamSynchronize(h->stream) != hipSuccess)
                 return release(PMF_EDEVICE);
+            const int64_t *f = (const int64_t *)back.data(), *sw = (const int64_t *)(back.data() + (o_st - o_f));
+            const int32_t *sts = (const int32_t *)(back.data() + (o_s - o_f));
+            for (int j = 0; j < m; ++j)
+                if (sts[j] != PMF_OK) return release(sts[j]);
             for (int j = 0; j < m; ++j) {
-                const Probe &pb = todo[b0 + j];
+                const Todo &pb = todo[b0 + j];
                 const Pair &pr = pb.pr;
                 const __int128 on_l = (__int128)pb.q * pr.L.a + (__int128)pr.L.w * pb.p;
                 if (f[j] == on_l) {
                     found.push_back(Found{pr.iv, pb.p, pb.q, pr.L, pr.R});
                 } else if (f[j] < on_l) {
-                    const int64_t wm = sw[2 * j + 1];
+                    const int64_t wm = sw[j];
                     const __int128 am = (__int128)f[j] - (__int128)wm * pb.p;
                     if (am % pb.q != 0) return release(PMF_EDEVICE);
                     const Line M{(int64_t)(am / pb.q), wm};
@@ -1996,23 +2023,22 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
     for (int i = 0; i < k; ++i) start[i + 1] = std::max(start[i + 1], start[i]);
     *n_bp = nb;
     if (launch_exit_pieces_init(exit_out, n, lam_lo, lam_hi, nb + 1, h->stream) != 0) return release(PMF_EDEVICE);
-    // each interval's breakpoints go to the start of the round area before
-    // its placement kernel (stream order keeps the previous one's reads)
+    // the breakpoints of as many intervals as fit go to the round area before
+    // their placement kernel (stream order keeps the previous one's reads)
     const size_t room = (size_t)R * probe_planes;
-    size_t at = 0;
-    for (int i = 0; i < k; ++i) {
-        const Interval &I = iv[i];
-        const int cnt = start[i + 1] - start[i];
-        const size_t bytes = 16 * (size_t)cnt;
-        if (at + bytes > room) at = 0;
-        if (bytes > room) return release(PMF_ENOMEM);
-        int64_t *dtab = (int64_t *)(scr + at);
-        if (hipMemcpyAsync(dtab, table.data() + 2 * (size_t)start[i], bytes, hipMemcpyHostToDevice, h->stream) !=
-                hipSuccess ||
-            launch_exit_place((const int32_t *)(pers + I.o_ep), (const int32_t *)(pers + I.o_eq), I.x0, I.y0, I.w,
-                              I.h, W, dtab, cnt, start[i], exit_out, h->stream) != 0)
+    for (int i0 = 0, i1; i0 < k; i0 = i1) {
+        for (i1 = i0; i1 < k && i1 - i0 < kProbeMasks && 16 * (size_t)(start[i1 + 1] - start[i0]) <= room; ++i1) {}
+        if (i1 == i0) return release(PMF_ENOMEM);
+        int nmax = 0;
+        IntervalTable t = table_of(i0, i1, &nmax);
+        for (int i = i0; i < i1; ++i) {
+            t.iv[i - i0].first = start[i];
+            t.iv[i - i0].count = start[i + 1] - start[i];
+        }
+        if (hipMemcpyAsync(scr, table.data() + 2 * (size_t)start[i0], 16 * (size_t)(start[i1] - start[i0]),
+                           hipMemcpyHostToDevice, h->stream) != hipSuccess ||
+            launch_exit_place(t, i1 - i0, nmax, W, (const int64_t *)scr, start[i0], exit_out, h->stream) != 0)
             return release(PMF_EDEVICE);
-        at = align_up(at + bytes);
     }
     return release(nb > max_bp ? PMF_ERANGE : PMF_OK);
 }
