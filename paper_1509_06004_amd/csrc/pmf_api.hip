@@ -1275,6 +1275,9 @@ int solve_batch(pmf_handle *h, const pmf_instance *inst, int32_t n_inst, int64_t
 
 namespace {
 
+// Probes of one round of the integer search: at most, and where memory is short.
+constexpr int kProbesMost = 256, kProbesFew = 64;
+
 // One solved lambda of a breakpoint search: its flow, |S_min| and slope sum
 // w(S_min) (the derivative of F on the piece where S_min is optimal).
 struct BpPoint {
@@ -1293,15 +1296,41 @@ int integer_breakpoints(pmf_handle *h, const pmf_instance &base, int32_t lam_lo,
     // solved lambda whose set lacks the pixel (every change point is solved,
     // and the set is constant between change points, so it is exact)
     if (exit_out && launch_fill_i32(exit_out, n, lam_hi + 1, h->stream) != 0) return PMF_EDEVICE;
+    // Device memory of a round of m probes: the largest layout the batched call
+    // can pick (every lambda a chunk of its own), without the round's own data.
+    auto layout_bytes = [&](int m) {
+        pmf_instance I = base;
+        I.L = m;
+        int64_t subs = 0;
+        const size_t pool1 = batch_pool_bytes(&I, 1, 1, h->tw, h->th, h->opt.gap != 0, &subs);
+        return control_bytes((int)subs, worklist_cap((int)subs, pool1)) + pool1;
+    };
+    // the round's own data: lambdas, flows, status, mask statistics
+    auto tail_bytes = [](int m) {
+        return align_up(4 * (size_t)m) + align_up(8 * (size_t)m) + align_up(4) + align_up(16 * (size_t)m);
+    };
+    // Whether m probes fit into what the handle may use without a doubt.
+    auto fits = [&](int m) {
+        const size_t need = layout_bytes(m) + tail_bytes(m);
+        if (need <= h->arena_bytes) return true;
+        if (!h->own_arena) return false;
+        if (h->opt.mem_budget > 0) return (int64_t)need <= h->opt.mem_budget;
+        size_t fr = 0, tot = 0;
+        return hipMemGetInfo(&fr, &tot) == hipSuccess && need <= (size_t)((double)(fr + h->arena_bytes) * 0.7);
+    };
     // Probes per round: the batched call solves them side by side, so a round
     // costs about as much as its slowest chunk until the device fills, and
-    // fewer, wider rounds win.  The budget shrinks for large images so that
-    // the round's state stays within 1 GiB.
-    int budget = 64;
+    // fewer, wider rounds win: 500 x 375 change points 51.9 / 44.0 / 36.1 ms
+    // with 32 / 64 / 128 (the most that 1 GiB takes), 320 x 240 breakpoints
+    // 35.3 / 31.4 / 28.7 / 23.9 ms with 32 / 64 / 128 / 256.  The budget shrinks for large images so that the
+    // round's state stays within 1 GiB, and to 64 where memory is short.
+    int budget = kProbesMost;
     for (pmf_instance I = base; budget > 2; budget /= 2) {
         I.L = budget;
         int64_t subs = 0;
-        if (batch_pool_bytes(&I, 1, 1, h->tw, h->th, h->opt.gap != 0, &subs) <= ((size_t)1 << 30)) break;
+        if (batch_pool_bytes(&I, 1, 1, h->tw, h->th, h->opt.gap != 0, &subs) <= ((size_t)1 << 30) &&
+            (budget <= kProbesFew || fits(budget)))
+            break;
     }
     // Solve the (ascending, distinct) lambdas of `lams` as the schedule of one
     // instance: the batched call splits it into warm-started chunks solved in
@@ -1313,14 +1342,11 @@ int integer_breakpoints(pmf_handle *h, const pmf_instance &base, int32_t lam_lo,
     auto solve = [&](const std::vector<int32_t> &lams) -> int {
         const int m = (int)lams.size();
         const size_t o_f = align_up(4 * (size_t)m), o_s = o_f + align_up(8 * (size_t)m), o_st = o_s + align_up(4),
-                     T = o_st + align_up(16 * (size_t)m);
+                     T = tail_bytes(m);
         pmf_instance I = base;
         I.L = m;
-        int64_t subs = 0;
-        const size_t pool1 = batch_pool_bytes(&I, 1, 1, h->tw, h->th, h->opt.gap != 0, &subs);
-        const size_t need = control_bytes((int)subs, worklist_cap((int)subs, pool1)) + pool1;
         h->reserve_tail = 0;
-        int rc = ensure_arena(h, need + T);
+        int rc = ensure_arena(h, layout_bytes(m) + T);
         if (rc != PMF_OK) return rc;
         h->reserve_tail = T;
         char *tail = h->arena + h->arena_bytes - T;
@@ -1422,6 +1448,12 @@ int integer_breakpoints(pmf_handle *h, const pmf_instance &base, int32_t lam_lo,
         }
         open.clear();
         if (live.empty()) break;
+        // more intervals than probes come to two each; where memory would not
+        // hold a round that wide, some intervals wait for the next
+        while (budget > kProbesFew && 2 * live.size() > (size_t)budget && !fits(2 * (int)live.size())) {
+            open.insert(open.end(), live.begin() + (ptrdiff_t)(live.size() / 2), live.end());
+            live.resize(live.size() / 2);
+        }
         const int k = std::max(2, budget / (int)live.size());
         std::vector<int32_t> mids;
         for (const auto &iv : live) probes(iv.first, iv.second, k, mids);
@@ -1840,8 +1872,8 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
         const int i1 = std::min(k, i0 + kProbeMasks);
         int nmax = 0;
         const IntervalTable t = table_of(i0, i1, &nmax);
-        if (launch_contract(t, i1 - i0, nmax, base.nlink, base.cap_src, base.cap_snk0, base.snk_slope, base.seed, W, H, K,
-                            exit_out, (int64_t *)(pers + o_stats) + (size_t)kCsStride * i0, h->stream) != 0)
+        if (launch_contract(t, i1 - i0, nmax, base.nlink, base.cap_src, base.cap_snk0, base.snk_slope, base.seed, W, H,
+                            K, exit_out, (int64_t *)(pers + o_stats) + (size_t)kCsStride * i0, h->stream) != 0)
             return release(PMF_EDEVICE);
     }
     if (hipMemcpyAsync(st_all.data(), pers + o_stats, 8 * st_all.size(), hipMemcpyDeviceToHost, h->stream) !=

@@ -47,3 +47,25 @@ def test_probe_tables(K, shape, span):
         assert int(fc) == int(pa[j]) + int(pw[j]) * c, c
     ceil_of = np.array([lo] + [math.ceil(x) for x in xs] + [hi + 1], dtype=np.int64)
     assert (ceil_of[ex.cpu().numpy()] == ex_i.cpu().numpy()).all()
+
+
+@pytest.mark.parametrize("mib", [4, 8, 24, 96])
+def test_search_in_limited_memory(mib):
+    """Rounds narrower than the widest, and intervals left for a later round,
+    where the memory limit asks for it: the same change points and exits."""
+    from paper_1509_06004_amd import pmf
+    inst = scattered(np.random.default_rng(mib), 33, 40, 4, 4000, seeded=True)
+    dev = pmf.to_device([inst])[0]
+    free = pmf.Solver()
+    want = pmf.pmf_parametric(free.handle, dev, 0, 4000)
+    free.close()
+    assert len(want[0]) > 256
+    tight = pmf.Solver(mem_budget=mib << 20)
+    try:
+        got = pmf.pmf_parametric(tight.handle, dev, 0, 4000)
+    except pmf.PmfError as exc:
+        assert exc.code == pmf.PMF_ENOMEM and mib < 96
+    else:
+        assert all(np.array_equal(np.asarray(g.cpu() if hasattr(g, "cpu") else g),
+                                  np.asarray(w.cpu() if hasattr(w, "cpu") else w)) for g, w in zip(got, want))
+    tight.close()
