@@ -224,6 +224,10 @@ struct pmf_handle {
     char *arena = nullptr;
     size_t arena_bytes = 0;
     bool own_arena = true;
+    // pinned memory that every handle has from the start: the counter block's
+    // copy, the staged launch parameters and small `poll` and `stage` areas
+    char *pinned_base = nullptr;
+    size_t pinned_bytes = 0;
     int32_t *pinned = nullptr;  // host-visible copy of the counter block (completions, list sizes, barrier)
     // host copy of what a wait reads back, laid out as on the device: the
     // states, the completion ring and the counter block; pinned memory that
@@ -243,7 +247,6 @@ struct pmf_handle {
     char *stage = nullptr;  // pinned memory for it
     size_t stage_cap = 0;
     std::vector<char> host_image;  // and the ordinary memory of an image too large for that
-    bool rounds_clean = false;     // the superstep count in the counter block is zero
     // session
     bool open = false;
     int max_slots = 0;
@@ -346,11 +349,20 @@ int ensure_arena(pmf_handle *h, size_t need) {
     return PMF_OK;
 }
 
+// Images and waits of up to kBulkBytes go through pinned memory in one copy;
+// every handle has kHostBytes of it for each from the start.
+constexpr size_t kBulkBytes = (size_t)1 << 20, kHostBytes = (size_t)64 << 10;
+
+// Give back a `poll` or `stage` area that has grown out of the first one.
+void free_pinned(pmf_handle *h, char *p) {
+    if (p && (p < h->pinned_base || p >= h->pinned_base + h->pinned_bytes)) (void)hipHostFree(p);
+}
+
 // Pinned host memory of at least `need` bytes in *p (capacity *cap): kept,
-// or replaced by a larger piece once the stream is idle.
-bool ensure_pinned(char **p, size_t *cap, size_t need) {
+// or replaced by a larger piece (the stream is idle).
+bool ensure_pinned(pmf_handle *h, char **p, size_t *cap, size_t need) {
     if (need <= *cap) return true;
-    if (*p) (void)hipHostFree(*p);
+    free_pinned(h, *p);
     *p = nullptr;
     *cap = 0;
     const size_t want = need + need / 4;
@@ -362,10 +374,6 @@ bool ensure_pinned(char **p, size_t *cap, size_t need) {
     *cap = want;
     return true;
 }
-
-// Images and waits of up to this many bytes go through pinned memory in one
-// copy; every handle has pinned memory for small ones from the start.
-constexpr size_t kBulkBytes = (size_t)1 << 20, kHostWords = (size_t)64 << 10;
 
 // Lay out the control area at the start of the arena and the pool after it
 // (or at the start of `ext_base`, ext_bytes of device memory handed in for
@@ -395,7 +403,7 @@ int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = n
     }
     const size_t b_st = align_up(sizeof(InstState) * (size_t)slots), b_ring = align_up(4 * (size_t)slots);
     h->poll_bytes = b_st + b_ring + align_up(256);
-    if (!h->ext && !ensure_pinned(&h->poll, &h->poll_cap, h->poll_bytes)) return PMF_ENOMEM;
+    if (!h->ext && !ensure_pinned(h, &h->poll, &h->poll_cap, h->poll_bytes)) return PMF_ENOMEM;
     h->poll_pinned = h->poll_bytes <= h->poll_cap;
     if (!h->poll_pinned) h->host_poll.resize(h->poll_bytes);
     char *poll = h->poll_pinned ? h->poll : h->host_poll.data();
@@ -454,12 +462,11 @@ int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = n
     h->trace.clear();
     h->stats.device_bytes = (int64_t)base_bytes;
     // every slot starts idle; the completion counter at zero
-    h->rounds_clean = true;
     if (table_bytes >= 0) {
         h->image_bytes = h->pool_base + (size_t)table_bytes - (size_t)((char *)P.desc - A);
         const bool pin = h->image_bytes <= h->stage_cap ||
                          (!h->ext && h->image_bytes <= kBulkBytes &&
-                          ensure_pinned(&h->stage, &h->stage_cap, h->image_bytes));
+                          ensure_pinned(h, &h->stage, &h->stage_cap, h->image_bytes));
         if (!pin) h->host_image.resize(h->image_bytes);
         h->image = pin ? h->stage : h->host_image.data();
         std::memset(h->image, 0, h->image_bytes);
@@ -705,8 +712,9 @@ int read_kernel_events(pmf_handle *h, int steps) {
 // instances of more than kEngineTiles tiles: one workgroup lists an
 // instance's tiles, and its claims go through one word, which costs more
 // there than a launch per superstep (1920 x 1080, 2040 tiles: 28.5 ms
-// against 24.9; 640 x 480, 300 tiles: 46.3 against 46.6 ms).  Its words are there for kEngineSlots instances from the handle's creation;
-// a longer work list gets more here, except in a solve that allocates nothing.
+// against 24.9; 640 x 480, 300 tiles: 46.3 against 46.6 ms).  Its words are
+// there for kEngineSlots instances from the handle's creation; a longer work
+// list gets more here, except in a solve that allocates nothing.
 bool engine_usable(pmf_handle *h) {
     const pmf_options &o = h->opt;
     const int n = h->P.nwl;
@@ -789,8 +797,6 @@ int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_
         E.avail = (unsigned long long *)(E.live + 8 * 32);
         E.sync = (int32_t *)(h->engine_mem + engine_clear_bytes(E.avail_words));
         E.quota = std::max(steps, persist_steps);
-        if (!h->rounds_clean && hipMemsetAsync(E.rounds, 0, 4, s) != hipSuccess) return PMF_EDEVICE;
-        h->rounds_clean = false;
         if (hipEventRecord(h->ev0, s) != hipSuccess) return PMF_EDEVICE;
         E.wgs = std::min(std::max(1, engine_wgs(h, kset)), P.ntiles);
         if (launch_engine(P, E, h->tw, kset, s) != 0) return PMF_EDEVICE;
@@ -1023,10 +1029,19 @@ int pmf_create(const pmf_options *opt, void *stream, void *workspace, size_t ws_
         h->arena_bytes = ws_bytes;
         h->own_arena = false;
     }
-    if (hipHostMalloc((void **)&h->pinned, 256, hipHostMallocDefault) != hipSuccess ||
-        hipHostMalloc((void **)&h->pinned_params, sizeof(StepParams), hipHostMallocDefault) != hipSuccess ||
-        !ensure_pinned(&h->poll, &h->poll_cap, kHostWords) || !ensure_pinned(&h->stage, &h->stage_cap, kHostWords) ||
-        hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking) != hipSuccess ||
+    h->pinned_bytes = 256 + align_up(sizeof(StepParams)) + 2 * kHostBytes;
+    if (hipHostMalloc((void **)&h->pinned_base, h->pinned_bytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        h->pinned_base = nullptr;
+        pmf_destroy(h);
+        return PMF_EDEVICE;
+    }
+    h->pinned = (int32_t *)h->pinned_base;
+    h->pinned_params = (StepParams *)(h->pinned_base + 256);
+    h->poll = h->pinned_base + 256 + align_up(sizeof(StepParams));
+    h->stage = h->poll + kHostBytes;
+    h->poll_cap = h->stage_cap = kHostBytes;
+    if (hipStreamCreateWithFlags(&h->capture, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreate(&h->ev0) != hipSuccess || hipEventCreate(&h->ev1) != hipSuccess) {
         (void)hipGetLastError();
         pmf_destroy(h);
@@ -2082,10 +2097,9 @@ int pmf_destroy(pmf_handle *h) {
     drop_graph(h);
     if (h->own_arena && h->arena) (void)hipFree(h->arena);
     if (h->engine_mem) (void)hipFree(h->engine_mem);
-    if (h->pinned) (void)hipHostFree(h->pinned);
-    if (h->pinned_params) (void)hipHostFree(h->pinned_params);
-    if (h->poll) (void)hipHostFree(h->poll);
-    if (h->stage) (void)hipHostFree(h->stage);
+    free_pinned(h, h->poll);
+    free_pinned(h, h->stage);
+    if (h->pinned_base) (void)hipHostFree(h->pinned_base);
     if (h->capture) (void)hipStreamDestroy(h->capture);
     if (h->ev0) (void)hipEventDestroy(h->ev0);
     if (h->ev1) (void)hipEventDestroy(h->ev1);

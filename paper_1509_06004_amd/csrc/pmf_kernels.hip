@@ -7,14 +7,17 @@
 // here from its textbook definition (Goldberg-Tarjan), with exact global
 // relabelling by breadth-first search (Cherkassky-Goldberg):
 //
-//   - a *superstep* is three launches: a compaction kernel lists the tiles
-//     that have work, a tile kernel processes them (each workgroup takes one
-//     TW x TH tile of one instance at a time and performs that instance's
-//     current phase on it), and a control kernel advances every instance's
-//     phase machine; supersteps are replayed from a captured graph with no
-//     host round trip in between;
-//   - kSweep: the tile's state is loaded into registers / LDS and up to
-//     `inner_iters` push/relabel iterations run against halo heights; pushes
+//   - a *superstep* of an instance lists its tiles that have work, processes
+//     them (a workgroup takes one TW x TH tile at a time and performs the
+//     instance's current phase on it) and advances its phase machine.  In the
+//     device-driven solve (k_engine) one launch runs every instance's
+//     supersteps, each instance at its own pace, tiles going to whichever
+//     workgroups are free.  Large instances and the measuring modes run
+//     supersteps of the whole batch as three launches (k_compact, k_step,
+//     k_control), replayed from a captured graph or launched directly;
+//   - kSweep: the tile's state is loaded into LDS and every active pixel's
+//     flow walks along lowest residual neighbours, lifting as it goes, for
+//     some `inner_iters` steps per active pixel against halo heights; pushes
 //     that leave the tile are accumulated and handed to the neighbour tile
 //     through its atomic inbox;
 //   - kRelabel: exact distances to t by tile-parallel Bellman-Ford relaxation
@@ -1882,7 +1885,8 @@ __device__ __forceinline__ bool eng_find(const StepParams &P, const EngineParams
         // Few instances and many idle workgroups: only some 64 per instance
         // look at its claim word (the others would queue up at it), twice as
         // many with every try.
-        if (total == 0 || (unsigned long long)(rnd >> 16) * wgs > (((unsigned long long)(64u * total) << imin((int)tries, 10)) << 16)) {
+        if (total == 0 || (unsigned long long)(rnd >> 16) * wgs >
+                              (((unsigned long long)(64u * total) << imin((int)tries, 10)) << 16)) {
             if (total == 0)
                 __builtin_amdgcn_s_sleep(64);
             else
@@ -2034,14 +2038,16 @@ __device__ __forceinline__ bool eng_advance(const StepParams &P, const EnginePar
     }
     // an instance with few tiles, next to few others, is latency bound: its
     // visits may run longer at no cost in width
-    const bool brief = (long long)count * (*s_live > D.ntiles ? *s_live : D.ntiles) < (long long)P.tail_tiles * D.ntiles;
+    const bool brief =
+        (long long)count * (*s_live > D.ntiles ? *s_live : D.ntiles) < (long long)P.tail_tiles * D.ntiles;
     // A claim's fixed cost (two atomics, a listing, two barriers: 2 us) is
     // shared by several tiles while each workgroup has many to come: a pass
     // visit is short (6 us), a sweep visit worth half as much sharing.  With
     // little left, single tiles spread better.  24 uneven images 73.7 -> 67.9
     // ms, 25 seeds x 20 lambdas 21.9 -> 21.3, 8-connected 29.9 -> 27.1.
     const int per = *s_live / E.wgs;  // running instances' tiles per workgroup
-    const int batch = imin(imax(phase != kSweep ? (per >= 8 ? 4 : per >= 4 ? 2 : 1) : per >= 16 ? 2 : 1, (count >> 9) + 1), kEngBatch);
+    const int share = phase != kSweep ? (per >= 8 ? 4 : per >= 4 ? 2 : 1) : per >= 16 ? 2 : 1;
+    const int batch = imin(imax(share, (count >> 9) + 1), kEngBatch);
     const uint32_t hi = claim_hi(count, *s_left, batch);
     const int own = take ? imin(batch, count) : 0;
     if (tid < kEngInfo) {
@@ -2056,7 +2062,9 @@ __device__ __forceinline__ bool eng_advance(const StepParams &P, const EnginePar
         st_agent(&sy[kSyInfo + tid], v);
         T->info[tid] = v;
     }
-    if (tid == 0) __hip_atomic_store((GLOBAL unsigned long long *)(sy + kSyDone), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0)
+        __hip_atomic_store((GLOBAL unsigned long long *)(sy + kSyDone), 0ull, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     // the bit goes up before the claim word: the last claimer of this
     // superstep clears it, and must not do so before it is set
     if (tid < 64 && count > own) eng_mark(E, w, true);
@@ -2074,8 +2082,17 @@ __device__ __forceinline__ bool eng_advance(const StepParams &P, const EnginePar
     return true;
 }
 
+// Before a launch: the copies of the bits and counts and the superstep count
+// are zeroed (one small launch; a fill of each cost a session's step another).
+__global__ __launch_bounds__(kThreads) void k_engine_clear(EngineParams E) {
+    const int n = (int)(engine_clear_bytes(E.avail_words) / 4);
+    const int i0 = (int)(blockIdx.x * kThreads + threadIdx.x);
+    for (int i = i0; i < n; i += (int)(gridDim.x * kThreads)) E.live[i] = 0;
+    if (i0 == 0) *E.rounds = 0;
+}
+
 // Start of a launch: one workgroup per instance of the work list publishes
-// its current superstep (the copies of the bits and counts were zeroed before).
+// its current superstep.
 __global__ __launch_bounds__(kThreads) void k_engine_start(StepParams P, EngineParams E) {
     __shared__ int32_t lds[kThreads];
     __shared__ int s_red[32];
@@ -2345,7 +2362,8 @@ int engine_workgroups(int tile_w, int kset) {
 int launch_engine(const StepParams &p, const EngineParams &e, int tile_w, int kset, void *stream) {
     if (e.wgs < 1 || p.nwl < 1 || p.nwl > 64 * e.avail_words) return -1;
     hipStream_t s = (hipStream_t)stream;
-    if (hipMemsetAsync(e.live, 0, engine_clear_bytes(e.avail_words), s) != hipSuccess) return -1;
+    const int words = (int)(engine_clear_bytes(e.avail_words) / 4);
+    hipLaunchKernelGGL(k_engine_clear, dim3(std::min((words + kThreads - 1) / kThreads, 64)), dim3(kThreads), 0, s, e);
     hipLaunchKernelGGL(k_engine_start, dim3(p.nwl), dim3(kThreads), 0, s, p, e);
     const void *fn = tile_w == 64 ? engine_fn<64, 16>(kset) : engine_fn<32, 32>(kset);
     void *args[] = {(void *)&p, (void *)&e};
