@@ -70,10 +70,11 @@ def bytes_per_px(K: int, tw: int = 32, th: int = 32) -> dict:
 
 
 def impl_bytes_per_px(K: int) -> dict:
-    """What this implementation moves per pixel visit (its passes read a
-    2-byte residual-bit word instead of the K + 1 residuals)."""
-    init = K * 4 + 13 + K * 4 + 12 + 2
-    return {"sweep": 2 * (K + 3) * 4 + 2, "relabel": 2 + 4 + 4, "cut": 2 + 1 + 1, "init": init,
+    """What this implementation moves per pixel visit at most (excess and sink
+    residual are one word, its passes read a 2-byte residual-bit word instead
+    of the K + 1 residuals, and a sweep writes back only the cells it changed)."""
+    init = K * 4 + 13 + K * 4 + 8 + 2
+    return {"sweep": 2 * (K + 2) * 4 + 2, "relabel": 2 + 4 + 4, "cut": 2 + 1 + 1, "init": init,
             "orient": 13, "init_x": init + K * 4, "cut_x": 4 + 2 + 4 + 4 + 1}
 
 

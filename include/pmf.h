@@ -58,10 +58,10 @@ enum pmf_status {
 typedef struct pmf_options {
     int32_t tile_w;             /* tile width in pixels: 32 or 64 (0 = default)     */
     int32_t tile_h;             /* tile height: tile_w * tile_h = 1024 (0 = default) */
-    int32_t inner_iters;        /* push/relabel iterations per tile visit            */
+    int32_t inner_iters;        /* push/relabel steps per active pixel and visit     */
     int32_t sweeps_per_relabel; /* sweep supersteps between global relabels          */
     int32_t local_bfs_iters;    /* bound on relaxation rounds between halo reads     */
-    int32_t steps_per_sync;     /* supersteps per host completion check              */
+    int32_t steps_per_sync;     /* launched supersteps per host completion check     */
     int64_t max_supersteps;     /* per-instance budget; exceeding it = PMF_ETIMEOUT  */
     int32_t use_graph;          /* 1: the device drives the solve: instances run     */
                                 /*   their supersteps inside one launch, tiles going */
