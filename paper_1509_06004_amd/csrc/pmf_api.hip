@@ -1255,7 +1255,11 @@ int solve_batch(pmf_handle *h, const pmf_instance *inst, int32_t n_inst, int64_t
     h->chunk = C;
     if (n_inst == 0) return PMF_OK;
     size_t moff = 0;
-    if (mbytes && !h->pool.alloc(mbytes, &moff)) return PMF_ENOMEM;
+    if (mbytes && !h->pool.alloc(mbytes, &moff)) {
+        h->open = false;  // the slots were never sent to the device
+        h->image = nullptr;
+        return PMF_ENOMEM;
+    }
     char *mbase = h->base + h->pool_base + moff;
     BatchEnd end{(const int32_t *)(mbase + tbytes), (const int64_t *)mbase, n_inst, flows_out, status_out, false};
     if (chunked) std::memcpy(in_image(h, mbase), meta.data(), 8 * meta.size());
