@@ -65,9 +65,11 @@ typedef struct pmf_options {
     int64_t max_supersteps;     /* per-instance budget; exceeding it = PMF_ETIMEOUT  */
     int32_t use_graph;          /* 1: the device drives the solve: instances run     */
                                 /*   their supersteps inside one launch, tiles going */
-                                /*   to whichever workgroups are free (instances of  */
-                                /*   up to 640 tiles; larger ones: supersteps        */
-                                /*   replayed from a captured hipGraph); 0: every    */
+                                /*   to whichever workgroups are free (not where an  */
+                                /*   instance has more than 640 tiles, or few        */
+                                /*   4-connected ones average more than 350: then    */
+                                /*   supersteps are replayed from a captured         */
+                                /*   hipGraph); 0: every                             */
                                 /*   superstep launched by the host                  */
     int32_t order;              /* 0: FIFO packing order, 1: LPT (largest first)     */
     int64_t mem_budget;         /* bytes the library may allocate (0 = no limit)     */

@@ -707,18 +707,41 @@ int read_kernel_events(pmf_handle *h, int steps) {
     return PMF_OK;
 }
 
+// Tiles per workgroup with which a work list keeps the device busy.
+constexpr int64_t kTilesPerWorkgroup = 40;
+// Average tiles of an instance of a 4-connected list above which a list with
+// fewer than that is launched superstep by superstep.
+constexpr int64_t kEngineMean = 350;
+
+// Workgroups of the device-driven launch, by work-list connectivity.
+int engine_wgs(pmf_handle *h, int kset) {
+    int &g = h->engine_grid[kset == 4 ? 0 : kset == 8 ? 1 : 2];
+    if (g == 0) g = engine_workgroups(h->tw, kset);
+    return g;
+}
+
 // Whether the work list is solved by the device-driven launch: every
-// instance then runs its supersteps without waiting for the others.  Not for
-// instances of more than kEngineTiles tiles: one workgroup lists an
-// instance's tiles, and its claims go through one word, which costs more
-// there than a launch per superstep (1920 x 1080, 2040 tiles: 28.5 ms
-// against 24.9; 640 x 480, 300 tiles: 46.3 against 46.6 ms).  Its words are
-// there for kEngineSlots instances from the handle's creation; a longer work
-// list gets more here, except in a solve that allocates nothing.
+// instance then runs its supersteps without waiting for the others, which is
+// what counts with many instances of few tiles (25 seeds x 20 lambdas of 500 x
+// 375, 192 tiles: 21.3 ms against 25.5 with separate launches, 8-connected
+// 27.1 against 37.4; 24 uneven images 67 against 109).  But one workgroup
+// lists an instance's tiles and all its claims go through one word, so large
+// instances are better launched: above kEngineTiles (1920 x 1080, 2040 tiles:
+// 26.2 against 18.1 ms; 1024 x 768, 768 tiles, six seeds 29.2 against 24.3),
+// and 4-connected lists whose instances hold more than kEngineMean tiles on
+// average (720 x 576, 414 tiles, eight seeds 15.9 against 13.3 ms, four of 20
+// lambdas 14.6 against 13.1, one 7.7 against 7.6; 640 x 480, 300 tiles, 25
+// seeds 26.7 against 27.0, one 6.6 against 7.1; 8-connected 414 tiles, four of
+// 20 lambdas, 18.5 against 21.2) unless the list keeps the device busy all the
+// same (800 x 600, 475 tiles, 16 seeds of 20 lambdas 36.0 against 39.1).  Its
+// words are there for kEngineSlots instances from the handle's creation; a
+// longer work list gets more here, except in a solve that allocates nothing.
 bool engine_usable(pmf_handle *h) {
     const pmf_options &o = h->opt;
     const int n = h->P.nwl;
     if (h->max_tiles > kEngineTiles) return false;
+    if (h->P.t8_count == 0 && h->P.ntiles > kEngineMean * n && h->P.ntiles < kTilesPerWorkgroup * engine_wgs(h, 4))
+        return false;
     if (h->P.ntiles <= 0 || !o.use_graph || o.timing != 0 || o.gap || o.persist_tiles != 0) return false;
     if (n <= h->engine_cap) return true;
     if (h->ext || n > kEngineMax) return false;
@@ -733,13 +756,6 @@ bool engine_usable(pmf_handle *h) {
     h->engine_mem = mem;
     h->engine_cap = want;
     return true;
-}
-
-// Workgroups of the device-driven launch, by work-list connectivity.
-int engine_wgs(pmf_handle *h, int kset) {
-    int &g = h->engine_grid[kset == 4 ? 0 : kset == 8 ? 1 : 2];
-    if (g == 0) g = engine_workgroups(h->tw, kset);
-    return g;
 }
 
 // What a batch's chunks come to: its instances' statuses (device pointers).
@@ -1133,8 +1149,6 @@ size_t batch_pool_bytes(const pmf_instance *inst, int n, int C, int tw, int th, 
 // 500x375 25-seed x 20-lambda batch: chunks of 2 lambdas at 4-connectivity
 // and of 3-4 at 8 were fastest; the rule picks 2 and 3, -7% and -20% against
 // chunks of 1).
-constexpr int64_t kTilesPerWorkgroup = 40;
-
 int64_t batch_tiles(const pmf_instance *inst, int n, int C, int tw, int th, int64_t *t8) {
     int64_t t = 0, e = 0;
     for (int i = 0; i < n; ++i) {
