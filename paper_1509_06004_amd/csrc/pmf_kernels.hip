@@ -46,6 +46,7 @@
 
 #include "pmf.h"
 #include "pmf_border.h"
+#include "pmf_claim.h"
 #include "pmf_internal.h"
 
 namespace pmf {
@@ -1764,8 +1765,8 @@ __global__ __launch_bounds__(kThreads) void k_persist(const StepParams *Pg, int 
 //
 // Per instance, three cache lines (EngineParams::sync) and a tile list (its
 // share of the list memory):
-//   claim  {count | superstep tag | batch, next}: one 64-bit add claims the
-//          next `batch` entries of the tile list
+//   claim  {count | superstep tag | batch, next}: one 64-bit add claims as
+//          many entries of the tile list as it adds (`batch`, as last seen)
 //   done   entries completed; the add that reaches count is the last
 //   info   what the superstep does (phase, pass number, lambda, iterations)
 // Per launch, one copy per XCD (polled by its own workgroups only): a bit per
@@ -1784,15 +1785,9 @@ __global__ __launch_bounds__(kThreads) void k_persist(const StepParams *Pg, int 
 // ---------------------------------------------------------------------------
 constexpr int kEngReplicas = 8;                  // one copy of the bits and the count per XCD
 constexpr long long kEngIdleTicks = 200000000;   // 2 s of the 100 MHz constant clock
-constexpr int kEngBatch = 16;
-
-// the high word of claim
-constexpr int kClCountBits = 20;
-__device__ __forceinline__ uint32_t claim_hi(int count, int tag, int batch) {
-    return (uint32_t)count | ((uint32_t)(tag & 255) << kClCountBits) | ((uint32_t)(batch - 1) << 28);
-}
-__device__ __forceinline__ int claim_count(uint32_t hi) { return (int)(hi & ((1u << kClCountBits) - 1)); }
-__device__ __forceinline__ int claim_batch(uint32_t hi) { return (int)(hi >> 28) + 1; }
+constexpr int kEngBatch = kClBatchMax;
+static_assert(kEngineTiles <= kClCountMax, "the claim word holds an instance's tiles");
+static_assert(kClTags > 65536, "and every superstep of a launch");
 
 // a workgroup's task, in LDS
 struct EngTask {
@@ -1826,16 +1821,16 @@ __device__ __forceinline__ void eng_live(const EngineParams &E, int d) {
     if (threadIdx.x < kEngReplicas) g_add(gp(E.live) + threadIdx.x * 32, d);
 }
 
-// The first wave takes the entries that a claim (`hi`, `next`) returned,
-// clearing the instance's bit with the last of them; false when none were
-// left.  pre: list entry pre_first + lane of the same superstep, if pre_hi == hi.
-__device__ __forceinline__ bool eng_take(const StepParams &P, const EngineParams &E, int w, int slot, uint32_t hi,
-                                         int next, uint32_t pre_hi, int pre_first, int pre, EngTask *T) {
+// The first wave takes the entries that a claim got, clearing the instance's
+// bit with the last of them; false when none were left.  pre: list entry
+// pre_first + lane of the same superstep, if pre_hi == c.hi.
+__device__ __forceinline__ bool eng_take(const StepParams &P, const EngineParams &E, int w, int slot, Claim c,
+                                         uint32_t pre_hi, int pre_first, int pre, EngTask *T) {
     const int lane = (int)(threadIdx.x & 63);
-    const int count = claim_count(hi), batch = claim_batch(hi);
-    if (next >= count) return false;
-    if (next + batch >= count) eng_mark(E, w, false);
-    const int n = imin(batch, count - next);
+    if (c.n == 0) return false;
+    if (c.last) eng_mark(E, w, false);
+    const uint32_t hi = c.hi;
+    const int next = c.first, n = c.n;
     const int at = next - pre_first;
     if (pre_hi == hi && at >= 0 && at + n <= 64) {
         if (lane >= at && lane < at + n) T->tile[lane - at] = pre;
@@ -1919,13 +1914,15 @@ __device__ __forceinline__ bool eng_find(const StepParams &P, const EngineParams
             __builtin_amdgcn_s_sleep(4);
             continue;
         }
+        // (the instance's next superstep may be published between the look and
+        // the add: the claim then takes that one's entries)
+        const int batch = __builtin_amdgcn_readfirstlane(claim_batch((uint32_t)(seen >> 32)));
         unsigned long long old = 0;
         if (lane == 0)
-            old = __hip_atomic_fetch_add(claim, (unsigned long long)claim_batch((uint32_t)(seen >> 32)),
-                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            old = __hip_atomic_fetch_add(claim, (unsigned long long)batch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(old >> 32));
-        const int next = __builtin_amdgcn_readfirstlane((int)(uint32_t)old);
-        if (eng_take(P, E, w, slot, hi, next, 0u, 0, 0, T)) return true;
+        const uint32_t next = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)old);
+        if (eng_take(P, E, w, slot, claim_take((uint64_t)hi << 32 | next, batch), 0u, 0, 0, T)) return true;
     }
     return false;
 }
@@ -2169,21 +2166,24 @@ __global__ __launch_bounds__(kThreads, KSET == 4 ? 4 : 3) void k_engine(StepPara
             const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_task.hi);
             const int first = __builtin_amdgcn_readfirstlane(s_task.first);
             GLOBAL const int32_t *list = gp(P.lists) + (size_t)desc_word(P.desc, slot, &InstDesc::tile0) * kEngLine;
+            const int batch = claim_batch(hi);
             unsigned long long old = 0;
             if (lane < 2) {
                 GLOBAL unsigned long long *p =
                     (GLOBAL unsigned long long *)(gp(E.sync) + (size_t)w * kEngSync + (lane == 0 ? kSyDone : kSyClaim));
-                old = __hip_atomic_fetch_add(p, (unsigned long long)(lane == 0 ? n : claim_batch(hi)), __ATOMIC_RELAXED,
+                old = __hip_atomic_fetch_add(p, (unsigned long long)(lane == 0 ? n : batch), __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
             }
             const int pre = ld_agent(&list[imin(first + lane, claim_count(hi) - 1)]);
             const int done = __builtin_amdgcn_readfirstlane((int)(uint32_t)old) + n;
             const uint32_t nhi = (uint32_t)__builtin_amdgcn_readlane((int)(old >> 32), 1);
-            const int next = __builtin_amdgcn_readlane((int)(uint32_t)old, 1);
+            const uint32_t next = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)old, 1);
             // (the superstep may have been completed by others and the
-            // instance's next one published in between: its tag differs)
+            // instance's next one published in between: its tag differs, and
+            // the claim takes that one's entries)
             const bool last = done == claim_count(hi);
-            const bool more = !last && eng_take(P, E, w, slot, nhi, next, hi, first, pre, &s_task);
+            const bool more =
+                !last && eng_take(P, E, w, slot, claim_take((uint64_t)nhi << 32 | next, batch), hi, first, pre, &s_task);
             if (lane == 0) s_task.last = last ? 2 : more ? 1 : 0;
         }
         __syncthreads();
