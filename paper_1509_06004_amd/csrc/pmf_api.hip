@@ -914,6 +914,10 @@ int run_steps(pmf_handle *h, int steps, std::vector<int> *finished, int persist_
         h->epoch_steps += ran;
     }
     if (engine) {
+        // A launch whose workgroups all gave up looking for work before any
+        // found some has changed nothing (an instance once begun is run to its
+        // end): not tried again here, 2 s at a time.
+        if (cb[kBarRounds] == 0 && (int64_t)P.nwl > h->wl_finished) return PMF_EDEVICE;
         h->stats.supersteps += cb[kBarRounds];
         h->epoch_steps += cb[kBarRounds];
     }

@@ -4,7 +4,9 @@ finished entries and claim again, publish the next superstep), every atomic a
 step of its own, is stepped through all interleavings of two or three
 consecutive supersteps with different batches.  Every entry of every superstep
 has to be taken exactly once, and no interleaving may come to a stop before
-the end.  The header is compiled with the host compiler."""
+the end.  With workgroups that may give up whenever they look for work, a run
+either is completed all the same or was never begun: no superstep is left
+half done.  The header is compiled with the host compiler."""
 
 import os
 import shutil
@@ -44,6 +46,7 @@ struct State {
 };
 std::vector<Step> steps;
 const char *fail = nullptr;
+bool give_up = false;  // a workgroup may leave whenever it looks for work
 
 uint64_t word(int s, int own) { return (uint64_t)claim_hi(steps[s].count, s, steps[s].batch) << 32 | (unsigned)own; }
 int step_of(uint32_t hi) { return (int)(hi >> kClCountBits) & (kClTags - 1); }
@@ -72,6 +75,12 @@ void advance(const State &s0, int i, std::vector<State> &out) {
     switch (g.pc) {
         case kLook:
             if (s.over) { g = Group{}; g.pc = kGone; break; }
+            if (give_up) {
+                State t = s;
+                t.g[i] = Group{};
+                t.g[i].pc = kGone;
+                out.push_back(t);
+            }
             if (!s.bit) return;  // polls
             g.hi = (uint32_t)(s.claim >> 32);
             if ((int)(uint32_t)s.claim >= claim_count(g.hi)) return;  // nothing left: polls
@@ -137,7 +146,8 @@ void advance(const State &s0, int i, std::vector<State> &out) {
 
 int main(int argc, char **argv) {
     const int nw = atoi(argv[1]);
-    for (int a = 2; a + 1 < argc; a += 2) steps.push_back(Step{atoi(argv[a]), atoi(argv[a + 1])});
+    give_up = atoi(argv[2]) != 0;
+    for (int a = 3; a + 1 < argc; a += 2) steps.push_back(Step{atoi(argv[a]), atoi(argv[a + 1])});
     State s0;
     std::memset(&s0, 0, sizeof(s0));
     s0.claim = word(0, 0);
@@ -156,8 +166,10 @@ int main(int argc, char **argv) {
         if (fail) { printf("%s\n", fail); return 1; }
         if (next.empty()) {
             for (int i = 0; i < kW; ++i) if (s.g[i].pc != kGone) { printf("stopped before the end\n"); return 2; }
+            size_t taken = 0, all = 0;
             for (size_t t = 0; t < steps.size(); ++t)
-                for (int e = 0; e < steps[t].count; ++e) if (s.taken[t][e] != 1) { printf("not taken\n"); return 3; }
+                for (int e = 0; e < steps[t].count; ++e) { ++all; taken += s.taken[t][e] == 1; }
+            if (taken != all && !(give_up && taken == 0 && (uint32_t)s.claim == 0)) { printf("half done\n"); return 3; }
             ++ends;
         }
         for (State &n : next) {
@@ -196,10 +208,10 @@ RUNS = [[(4, 1), (4, 2)], [(4, 2), (9, 4)], [(5, 4), (6, 2)], [(5, 4), (3, 1)], 
         [(3, 2), (3, 1), (3, 2)], [(4, 2), (1, 1), (7, 4)]]
 
 
-@pytest.mark.parametrize("groups", [2, 3])
+@pytest.mark.parametrize("groups,give_up", [(2, 0), (3, 0), (3, 1)])
 @pytest.mark.parametrize("run", RUNS, ids=str)
-def test_every_entry_is_taken_once(model, run, groups):
-    args = [str(groups)] + [str(x) for s in run for x in s]
+def test_every_entry_is_taken_once(model, run, groups, give_up):
+    args = [str(groups), str(give_up)] + [str(x) for s in run for x in s]
     r = subprocess.run([model] + args, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0, (r.returncode, r.stdout, r.stderr)
 
