@@ -67,7 +67,9 @@ typedef struct pmf_options {
                                 /*   their supersteps inside one launch, tiles going */
                                 /*   to whichever workgroups are free (not where an  */
                                 /*   instance has more than 640 tiles, or few        */
-                                /*   4-connected ones average more than 350: then    */
+                                /*   4-connected ones average more than 350, nor     */
+                                /*   where images of under some 50 x 50 pixels fill  */
+                                /*   the memory limit to the last KiB: then          */
                                 /*   supersteps are replayed from a captured         */
                                 /*   hipGraph); 0: every                             */
                                 /*   superstep launched by the host                  */

@@ -113,13 +113,29 @@ BlockLayout block_layout(const pmf_instance &I, int tw, int th, bool gap) {
 // at least 512 bytes, so the pool can never hold more tiles than this.
 size_t worklist_cap(int slots, size_t pool_bytes) { return pool_bytes / 512 + (size_t)slots; }
 
-// The device-driven solve keeps an instance's tile list (4 bytes per tile) in
-// the list memory, whose 32 bytes per work-list
-// entry are dealt out by the instance's place in the pool: the block at
+// The device-driven solve has its tile lists and its words in the list memory,
+// which it uses instead of the launches' four lists (32 bytes per work-list
+// entry).  The lists (4 bytes per tile) take the first half of those bytes,
+// dealt out by the instance's place in the pool: the block at
 // [off, off + bytes) owns the 64-byte lines [engine_list_at(off), engine_list_at(off +
 // bytes)).  A block of one tile has at least 2816 bytes and every further
-// tile adds 512, so a share holds at least 4 bytes per tile.
-int32_t engine_list_at(size_t off) { return (int32_t)(((off / 512) * 32 + 63) / 64); }
+// tile adds 512, so n tiles share at least 16 n + 16 bytes of whole lines.
+int32_t engine_list_at(size_t off) { return (int32_t)(((off / 512) * 16 + 63) / 64); }
+size_t engine_lists_bytes(size_t wl) { return align_up(16 * wl); }
+
+// Whether the options leave solves to the device.
+bool engine_options(const pmf_options &o) {
+    return o.use_graph != 0 && o.timing == 0 && o.gap == 0 && o.persist_tiles == 0;
+}
+
+// What the words of `slots` instances need beyond the rest of the list memory
+// of `wl` entries: nothing for images of more than some 50 x 50 pixels.  List
+// memory is made larger by this where the memory limits have room for it.
+size_t engine_more(const pmf_options &o, int slots, size_t wl) {
+    const size_t room = align_up(4 * 8 * wl) - engine_lists_bytes(wl);
+    const size_t want = engine_bytes(std::min(slots, kEngineMax));
+    return engine_options(o) && want > room ? align_up(want - room) : 0;
+}
 
 // Device bytes of the control area for `slots` slots and a work list of `wl` tiles.
 size_t control_bytes(int slots, size_t wl) {
@@ -292,8 +308,8 @@ struct pmf_handle {
     // device-driven solve: workgroups of its launch by work-list connectivity
     // (4 only, 8 only, mixed; 0: not looked up yet) and its device words
     int engine_grid[3] = {0, 0, 0};
-    char *engine_mem = nullptr;
-    int engine_cap = 0;  // instances it has room for
+    char *engine_mem = nullptr;  // part of the list memory
+    size_t engine_room = 0;
     int max_tiles = 0;   // tiles of the largest instance of the work list
     int64_t last_listed = -1;
     bool poisoned = false;
@@ -349,6 +365,15 @@ int ensure_arena(pmf_handle *h, size_t need) {
     return PMF_OK;
 }
 
+// The same, with `more` bytes beyond where the limits allow them.
+int ensure_arena_with(pmf_handle *h, size_t need, size_t more) {
+    if (more && need + more > h->arena_bytes && h->own_arena &&
+        (h->opt.mem_budget == 0 || (int64_t)(need + more) <= h->opt.mem_budget) &&
+        ensure_arena(h, need + more) == PMF_OK)
+        return PMF_OK;
+    return ensure_arena(h, need);
+}
+
 // Images and waits of up to kBulkBytes go through pinned memory in one copy;
 // every handle has kHostBytes of it for each from the start.
 constexpr size_t kBulkBytes = (size_t)1 << 20, kHostBytes = (size_t)64 << 10;
@@ -388,7 +413,7 @@ int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = n
     h->image = nullptr;
     (void)hipStreamSynchronize(h->stream);
     const size_t wl = worklist_cap(slots, pool_bytes);
-    const size_t ctl = control_bytes(slots, wl);
+    const size_t ctl = control_bytes(slots, wl), more = engine_more(h->opt, slots, wl);
     h->ext = ext_base != nullptr;
     size_t base_bytes = 0;
     if (h->ext) {
@@ -396,7 +421,8 @@ int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = n
         h->base = ext_base;
         base_bytes = ext_bytes;
     } else {
-        int rc = ensure_arena(h, ctl + pool_bytes + h->reserve_tail);
+        // (memory at the end of the arena in use: it stays where it is)
+        int rc = ensure_arena_with(h, ctl + pool_bytes + h->reserve_tail, h->reserve_tail ? 0 : more);
         if (rc != PMF_OK) return rc;
         h->base = h->arena;
         base_bytes = h->arena_bytes - h->reserve_tail;
@@ -419,7 +445,10 @@ int open_session(pmf_handle *h, int slots, size_t pool_bytes, char *ext_base = n
     };
     StepParams &P = h->P;
     std::memset(&P, 0, sizeof(P));
-    P.lists = (int32_t *)take(4 * 8 * wl);
+    const size_t list_bytes = align_up(4 * 8 * wl) + (ctl + pool_bytes + more <= base_bytes ? more : 0);
+    P.lists = (int32_t *)take(list_bytes);
+    h->engine_mem = (char *)P.lists + engine_lists_bytes(wl);
+    h->engine_room = list_bytes - engine_lists_bytes(wl);
     h->P_dev = (StepParams *)take(sizeof(StepParams));
     // these five are one copy to the device when a batch starts, and the
     // states, the ring and the counter block one copy back after each launch
@@ -733,29 +762,13 @@ int engine_wgs(pmf_handle *h, int kset) {
 // lambdas 14.6 against 13.1, one 7.7 against 7.6; 640 x 480, 300 tiles, 25
 // seeds 26.7 against 27.0, one 6.6 against 7.1; 8-connected 414 tiles, four of
 // 20 lambdas, 18.5 against 21.2) unless the list keeps the device busy all the
-// same (800 x 600, 475 tiles, 16 seeds of 20 lambdas 36.0 against 39.1).  Its
-// words are there for kEngineSlots instances from the handle's creation; a
-// longer work list gets more here, except in a solve that allocates nothing.
+// same (800 x 600, 475 tiles, 16 seeds of 20 lambdas 36.0 against 39.1).
 bool engine_usable(pmf_handle *h) {
-    const pmf_options &o = h->opt;
     const int n = h->P.nwl;
     if (h->max_tiles > kEngineTiles) return false;
     if (h->P.t8_count == 0 && h->P.ntiles > kEngineMean * n && h->P.ntiles < kTilesPerWorkgroup * engine_wgs(h, 4))
         return false;
-    if (h->P.ntiles <= 0 || !o.use_graph || o.timing != 0 || o.gap || o.persist_tiles != 0) return false;
-    if (n <= h->engine_cap) return true;
-    if (h->ext || n > kEngineMax) return false;
-    const int want = std::min(kEngineMax, n + n / 2);
-    char *mem = nullptr;
-    if (hipMalloc((void **)&mem, engine_bytes(want)) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    (void)hipStreamSynchronize(h->stream);
-    if (h->engine_mem) (void)hipFree(h->engine_mem);
-    h->engine_mem = mem;
-    h->engine_cap = want;
-    return true;
+    return h->P.ntiles > 0 && engine_options(h->opt) && n <= kEngineMax && engine_bytes(n) <= h->engine_room;
 }
 
 // What a batch's chunks come to: its instances' statuses (device pointers).
@@ -1067,12 +1080,6 @@ int pmf_create(const pmf_options *opt, void *stream, void *workspace, size_t ws_
         pmf_destroy(h);
         return PMF_EDEVICE;
     }
-    if (hipMalloc((void **)&h->engine_mem, engine_bytes(kEngineSlots)) == hipSuccess) {
-        h->engine_cap = kEngineSlots;
-    } else {
-        (void)hipGetLastError();
-        h->engine_mem = nullptr;  // supersteps as separate launches
-    }
     h->scratch_dev = scratch_address(h->device);
     if (o.persist_tiles > 0) {
         int cus = 0;
@@ -1383,7 +1390,7 @@ int integer_breakpoints(pmf_handle *h, const pmf_instance &base, int32_t lam_lo,
         pmf_instance I = base;
         I.L = m;
         h->reserve_tail = 0;
-        int rc = ensure_arena(h, layout_bytes(m) + T);
+        int rc = ensure_arena_with(h, layout_bytes(m) + T, engine_options(h->opt) ? align_up(engine_bytes(m)) : 0);
         if (rc != PMF_OK) return rc;
         h->reserve_tail = T;
         char *tail = h->arena + h->arena_bytes - T;
@@ -1883,7 +1890,7 @@ int pmf_breakpoints(pmf_handle *h, const pmf_instance *inst, int32_t lam_lo, int
     int R = 64;
     while (R > 1 && round_pool(R) + round_scratch(R) > ((size_t)1 << 30)) R /= 2;
     const size_t T = P + round_scratch(R);
-    rc = ensure_arena(h, round_pool(R) + T);
+    rc = ensure_arena_with(h, round_pool(R) + T, engine_options(h->opt) ? align_up(engine_bytes(R)) : 0);
     if (rc != PMF_OK) return release(rc);
     h->reserve_tail = T;
     char *pers = h->arena + h->arena_bytes - T, *scr = pers + P;
@@ -2118,7 +2125,6 @@ int pmf_destroy(pmf_handle *h) {
     (void)hipStreamSynchronize(h->stream);
     drop_graph(h);
     if (h->own_arena && h->arena) (void)hipFree(h->arena);
-    if (h->engine_mem) (void)hipFree(h->engine_mem);
     free_pinned(h, h->poll);
     free_pinned(h, h->stage);
     if (h->pinned_base) (void)hipHostFree(h->pinned_base);

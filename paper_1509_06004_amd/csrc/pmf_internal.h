@@ -172,9 +172,9 @@ int launch_persist(const StepParams *p_dev, int tile_w, int kset, int grid, int 
 
 // The device-driven solve: one launch in which every instance of the work
 // list runs up to `quota` supersteps of its own (tiles claimed by whichever
-// workgroups are free).  Memory: engine_bytes() for the words below, and the
-// list memory of StepParams for the tile lists, where InstDesc::tile0 is the
-// 64-byte line at which the instance's share starts.
+// workgroups are free).  Memory: that of StepParams::lists, which holds the tile
+// lists (InstDesc::tile0 is the 64-byte line at which the instance's share
+// starts) and then engine_bytes() for the words below.
 struct EngineParams {
     int32_t *live;        // [8 * 32] per XCD: tiles of the instances still running (one word per 128 bytes)
     int32_t *rounds;      // most supersteps an instance ran in this launch (a word of the counter block)
@@ -191,8 +191,7 @@ constexpr int kEngLine = 16;  // words of a line of the list memory
 constexpr size_t engine_clear_bytes(int avail_words) { return 8 * 128 + 8 * (size_t)avail_words * 8; }
 constexpr int engine_words(int n) { return (n + 1023) / 1024 * 16; }
 constexpr size_t engine_bytes(int n) { return engine_clear_bytes(engine_words(n)) + (size_t)n * kEngSync * 4; }
-constexpr int kEngineSlots = 4096;    // instances that every handle has room for from the start
-constexpr int kEngineMax = 1 << 16;   // and at most
+constexpr int kEngineMax = 1 << 16;   // instances at most
 constexpr int kEngineTiles = 640;     // tiles of the largest instance it is used for
 // Workgroups of that launch that the current device holds at once (0 if the
 // runtime cannot tell); kset: 4 or 8 when every instance of the work list has
