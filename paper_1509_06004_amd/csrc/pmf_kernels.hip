@@ -743,7 +743,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
         int moved = s_moved[c];
 #pragma unroll
         for (int k = 0; k < K; ++k) moved |= s_moved[c + DYk(k) * HW + DXk(k)];
-        if (!moved) continue;  // as it was
+        if (!moved && !killed[j]) continue;  // as it was (a stopped pixel keeps kHInf)
         int rm = x_bits(e);
 #pragma unroll
         for (int k = 0; k < K; ++k) {
