@@ -554,6 +554,9 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
     // Hand pushes into halo cells to the neighbour tiles' inboxes (the word k
     // of halo cell q with q + d_k inside the tile holds what q received) and
     // clear those words; the neighbour tiles are marked for the wake-up below.
+    // The excess words of those cells start afresh too: between two exchanges a
+    // cell receives at most 3 * 2 * PMF_NLINK_MAX(K), but over many it could
+    // pass 2^31, come round to zero and be taken for a pixel of the tile.
     auto flush_halo = [&]() {
         for (int i = tid; i < G::RING; i += kThreads) {
             int hx, hy;
@@ -574,6 +577,7 @@ __device__ __forceinline__ void sweep_tile(const StepParams &P, const InstDesc &
                     const int nt = (ty + dty - 1) * D.tiles_x + tx + dtx - 1;
                     g_add(&gp(D.inbox)[(size_t)nt * B::E + B::index(bx, by, k)], v);
                     sh_r[c * K + k] = 0;
+                    sh_e[c] = 1;
                     s_nb[dty * 3 + dtx] = 1;
                 }
             }
