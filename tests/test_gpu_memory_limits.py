@@ -127,3 +127,40 @@ def test_workspaces_from_just_enough_to_ample(name):
         lo, hi = (lo, mid) if accepted(mid) else (mid, hi)
     for more in (256, 1024, 2048, 4096, 16384, 65536):
         assert accepted(min(ample, hi + more))
+
+
+@pytest.mark.parametrize("probes,narrow", [(1, None), (2, None), (64, None), (130, True), (300, False)])
+def test_searches_within_budgets(probes, narrow):
+    """A search of more than 256 change points under budgets given in probes
+    of its image: room for 128 side by side but not for 256 narrows the rounds
+    and leaves intervals for later ones, half a probe's room is too little."""
+    from paper_1509_06004_amd import pmf
+    rng = np.random.default_rng(4000)
+    inst = W.tiny_random(rng, 33, 40, 4, cmax=3, L=1, p_seed=0.03, lam_max=50)
+    inst.cap_src = rng.integers(0, 4000, size=(40, 33)).astype(np.int32)
+    inst.cap_snk0 = rng.integers(0, 4, size=(40, 33)).astype(np.int32)
+    inst.snk_slope = rng.integers(1, 4, size=(40, 33)).astype(np.int32)
+    dev = pmf.to_device([inst])[0]
+    free = pmf.Solver()
+    want = pmf.pmf_parametric(free.handle, dev, 0, 4000)
+    free.close()
+    assert len(want[0]) > 256
+    # a probe's state, its share of the control area and of the round's own data
+    per = pmf.pmf_query_bytes([dev.c_struct()]) * 17 // 16 + 1024
+    too_little = pmf.Solver(mem_budget=per // 2)
+    with pytest.raises(pmf.PmfError) as exc:
+        pmf.pmf_parametric(too_little.handle, dev, 0, 4000)
+    assert exc.value.code == pmf.PMF_ENOMEM
+    too_little.close()
+    s = pmf.Solver(mem_budget=per * probes + 16384)
+    try:
+        got = pmf.pmf_parametric(s.handle, dev, 0, 4000)
+    except pmf.PmfError as exc:
+        # rounds of two probes an interval are not narrowed below 128
+        assert exc.code == pmf.PMF_ENOMEM and narrow is None
+    else:
+        for g, w in zip(got, want):
+            assert np.array_equal(np.asarray(g.cpu() if hasattr(g, "cpu") else g),
+                                  np.asarray(w.cpu() if hasattr(w, "cpu") else w))
+        assert s.stats()["device_bytes"] <= per * probes + 16384
+    s.close()
