@@ -760,9 +760,16 @@ int engine_wgs(pmf_handle *h, int kset) {
 // and 4-connected lists whose instances hold more than kEngineMean tiles on
 // average (720 x 576, 414 tiles, eight seeds 15.9 against 13.3 ms, four of 20
 // lambdas 14.6 against 13.1, one 7.7 against 7.6; 640 x 480, 300 tiles, 25
-// seeds 26.7 against 27.0, one 6.6 against 7.1; 8-connected 414 tiles, four of
-// 20 lambdas, 18.5 against 21.2) unless the list keeps the device busy all the
-// same (800 x 600, 475 tiles, 16 seeds of 20 lambdas 36.0 against 39.1).
+// seeds 26.7 against 27.0, one 6.6 against 7.1) unless the list keeps the device
+// busy all the same (800 x 600, 475 tiles, 16 seeds of 20 lambdas 36.0 against
+// 39.1).  8-connected lists are better off here up to the 640 tiles (geometric
+// means of three images, four seeds of 20 lambdas: 414 tiles 21.3 against 23.9,
+// 475 21.5 against 23.1, 520 29.1 against 31.2, 640 26.8 against 29.6; a single
+// one at 520 and 640 tiles 10.3 and 15.5 against 9.6 and 15.5), and so are lists
+// of both connectivities, whose supersteps are two launches of tile work each
+// (eight seeds of 720 x 576 and one small 8-connected image 10.2 against 10.8,
+// four of 20 lambdas with one 12.7 against 13.6, four of each kind 9.9 against
+// 12.5).
 bool engine_usable(pmf_handle *h) {
     const int n = h->P.nwl;
     if (h->max_tiles > kEngineTiles) return false;

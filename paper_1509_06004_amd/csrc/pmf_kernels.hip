@@ -1789,7 +1789,8 @@ __global__ __launch_bounds__(kThreads) void k_persist(const StepParams *Pg, int 
 // ---------------------------------------------------------------------------
 constexpr int kEngReplicas = 8;                  // one copy of the bits and the count per XCD
 constexpr long long kEngIdleTicks = 200000000;   // 2 s of the 100 MHz constant clock
-constexpr int kEngBatch = kClBatchMax;
+constexpr int kEngBatch = 4;                     // entries of a claim at most
+static_assert(kEngBatch <= kClBatchMax && (kEngineTiles >> 9) + 1 <= kEngBatch, "as eng_advance chooses");
 static_assert(kEngineTiles <= kClCountMax, "the claim word holds an instance's tiles");
 static_assert(kClTags > 65536, "and every superstep of a launch");
 
@@ -2049,10 +2050,12 @@ __device__ __forceinline__ bool eng_advance(const StepParams &P, const EnginePar
     // shared by several tiles while each workgroup has many to come: a pass
     // visit is short (6 us), a sweep visit worth half as much sharing.  With
     // little left, single tiles spread better.  24 uneven images 73.7 -> 67.9
-    // ms, 25 seeds x 20 lambdas 21.9 -> 21.3, 8-connected 29.9 -> 27.1.
+    // ms, 25 seeds x 20 lambdas 21.9 -> 21.3, 8-connected 29.9 -> 27.1.  A list
+    // of 512 tiles or more goes out in twos at the least (20 lambdas of 1024 x
+    // 640, 640 tiles: 14.9 ms against 15.1 in ones, 4-connected 10.9 against 11.1).
     const int per = *s_live / E.wgs;  // running instances' tiles per workgroup
     const int share = phase != kSweep ? (per >= 8 ? 4 : per >= 4 ? 2 : 1) : per >= 16 ? 2 : 1;
-    const int batch = imin(imax(share, (count >> 9) + 1), kEngBatch);
+    const int batch = imax(share, (count >> 9) + 1);
     const uint32_t hi = claim_hi(count, *s_left, batch);
     const int own = take ? imin(batch, count) : 0;
     if (tid < kEngInfo) {
