@@ -172,6 +172,8 @@ def roofline(dev, overrides: dict, K: int, pmf, torch, split: bool = True) -> di
     achieved = d["alg_bytes_per_launch"] / (d["avg_launch_us"] * 1e-6) / 1e9
     out = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
            "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None, "kernel": dom,
+           "what": "the tile work in separate launches (a solve in timing mode); the timed steps run the same "
+                   "code inside k_engine, their rate is per_step.alg_GBs_over_device_time",
            "avg_launch_us": d["avg_launch_us"], "alg_bytes_per_launch": d["alg_bytes_per_launch"],
            "launches": d["launches"], "bytes_per_px": b, "impl_bytes_per_px": bi, "kernels": kernels,
            "supersteps": st["supersteps"], "device_ms": round(st["device_ns"] / 1e6, 3)}
@@ -472,7 +474,9 @@ def main():
            "per_step": {"supersteps": last["supersteps"], "persist_supersteps": last["persist_supersteps"],
                         "host_syncs": last["host_syncs"],
                         "px_visits": {k: last["px_" + k] for k in KINDS},
-                        "alg_GB": round(stat_bytes(last, bytes_per_px(4)) / 1e9, 3)},
+                        "alg_GB": round(stat_bytes(last, bytes_per_px(4)) / 1e9, 3),
+                        "alg_GBs_over_device_time": round(stat_bytes(last, bytes_per_px(4)) /
+                                                          max(last["device_ns"], 1), 1)},
            "autotuned": tuned}
 
     if not args.no_transfers:

@@ -20,7 +20,7 @@ import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # the sources the device code is compiled from
-KERNEL_SOURCES = [os.path.join(HERE, "csrc", f) for f in ("pmf_kernels.hip", "pmf_border.h", "pmf_internal.h")]
+KERNEL_SOURCES = [os.path.join(HERE, "csrc", f) for f in ("pmf_kernels.hip", "pmf_border.h", "pmf_claim.h", "pmf_internal.h")]
 
 
 def source_hash() -> str:
